@@ -138,7 +138,11 @@ struct PredictArgs {
   float threshold;          // predicted class 1 when Out >= threshold
   float* out;               // [n x NP] (prediction)
   int64_t* counts;          // [n x 4]: TP, FP, TN, FN (classification)
+  // Classification sums of up to kTallyChromosomes chromosomes ([n x 4]),
+  // zero between launches.
+  unsigned long long* tally;
 };
+constexpr int kTallyChromosomes = 1024;
 hipError_t launch_predict(const PredictArgs& a, int basis, hipStream_t s);
 
 struct Rescore64Args {

@@ -2,101 +2,165 @@
 // of merit): the model output Out (Eq. 2) of given chromosomes on a set of
 // patterns, stored, or turned into class decisions and counted.
 //
-// These are not on the training loop's hot path, so one thread computes one
-// (pattern, chromosome) output on the vector ALUs in float32, in the
-// canonical gene order (feature, block, degree) with fused multiply-adds;
-// the chromosome's genes sit in LDS.  Prediction and classification share
-// the same output routine, so a class decision equals the stored output
-// compared with the threshold.
+// Each output is one chain of float32 fused multiply-adds in the canonical
+// gene order (feature, block, degree) on the vector ALUs.  Prediction and
+// classification share the output routine, so a class decision equals the
+// stored output compared with the threshold.
+//
+// A thread owns one pattern and R chromosomes at a time, so an expansion
+// value feeds R chains.  The genes are uniform over a workgroup and come in
+// by scalar loads, one SGPR operand per multiply-add; the degree is a
+// template argument, so the recurrence's coefficients are constants.  The
+// patterns' rows are read in consecutive addresses into LDS (odd row stride:
+// conflict-free) and serve every chromosome group of the workgroup.  Bound
+// by the vector multiply-adds for 8 chromosomes and by reading the patterns
+// for one.  1,000,000 x 20 patterns, Legendre 8: 25 us for one chromosome
+// (80 MB of patterns, 4 MB of outputs: 3.4 TB/s), 57 us for 8, 367 us for 64
+// (56 TFLOP/s of multiply-adds); with one thread per (pattern, chromosome),
+// a run-time degree and a row read per output they took 125, 728 and 5,580.
+#include <algorithm>
+#include <utility>
+
 #include "basis.h"
-#include "common.h"
+#include "rows.h"
 
 namespace game {
 
 namespace {
 
-// Out for one pattern row x[0..N) of a chromosome w[0..K) (runtime degree).
-template <int BASIS>
-__device__ float model_output(const float* x, int N, int d, const float* w) {
+// out[r] of this thread's pattern (row threadIdx.x of the tile) for the
+// chromosomes of group grp (the last one repeated past n).  `staged` tells
+// whether LDS holds the tile's whole rows already.
+template <int BASIS, int D, int R, bool STAGE>
+__device__ __forceinline__ void tile_outputs(const PredictArgs& a, float* rows, int grp,
+                                             int64_t row0, int n_rows, bool& staged,
+                                             float (&out)[R]) {
   constexpr int B = BASIS == 3 ? 2 : 1;
-  float out = w[0];
-  for (int f = 0; f < N; ++f) {
-    const float xv = x[f];
-    for (int b = 0; b < B; ++b) {
-      const float* wf = w + 1 + (f * B + b) * d;
-      float prev, cur, m2 = 2.f * xv;
-      if constexpr (BASIS == 3) {
-        float s, c;
-        sincosf(xv, &s, &c);
-        prev = b ? 0.f : 1.f;
-        cur = b ? s : c;
-        m2 = 2.f * c;
-      } else {
-        prev = 1.f;
-        cur = xv;
-      }
-      for (int j = 1; j <= d; ++j) {
-        out = fmaf(wf[j - 1], cur, out);
-        if (j == d) break;
-        float nx;
-        if constexpr (BASIS == 0 || BASIS == 3) {
-          nx = fmaf(m2, cur, -prev);
-        } else if constexpr (BASIS == 1) {
-          // (j+1) P_{j+1} = (2j+1) x P_j - j P_{j-1}
-          const float a = (float)(2 * j + 1) / (float)(j + 1), c = (float)j / (float)(j + 1);
-          nx = fmaf(a * xv, cur, -c * prev);
-        } else {
-          nx = cur * xv;
-        }
-        prev = cur;
-        cur = nx;
+  const int N = a.N;
+  const int FC = STAGE ? min(N, kChunk) : N;
+  const int S = row_stride(FC);
+  const float* mine = STAGE ? rows + threadIdx.x * S
+                            : a.X + (row0 + min((int)threadIdx.x, n_rows - 1)) * N;
+  ConstGene* w[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    w[r] = (ConstGene*)a.genes + (int64_t)min(grp * R + r, a.n - 1) * a.K;
+    out[r] = w[r][0];
+  }
+  for (int f0 = 0; f0 < N; f0 += FC) {
+    const int nf = min(FC, N - f0);
+    if (STAGE && !staged) {
+      __syncthreads();            // the rows staged before have been used
+      stage_rows(rows, S, a.X, row0, n_rows, N, f0, nf);
+      __syncthreads();
+      staged = FC == N;
+    }
+    // Several features' scalar gene loads in flight (as many as about 64
+    // SGPRs hold): a small set's few waves otherwise wait out each one.
+    constexpr int kAhead = std::clamp(64 / (R * B * D), 1, 8);
+#pragma unroll kAhead
+    for (int fi = 0; fi < nf; ++fi) {
+      const float x = mine[fi];
+      const int at = 1 + (f0 + fi) * B * D;
+      float c = 0.f, s = 0.f;
+      if constexpr (BASIS == 3) sincosf(x, &s, &c);
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        Recur<BASIS> rc;
+        if constexpr (BASIS == 3) rc.seed_cs(c, s, b);
+        else rc.seed(x, 0);
+        auto term = [&](auto jc) {
+          constexpr int j = decltype(jc)::value;
+#pragma unroll
+          for (int r = 0; r < R; ++r) out[r] = fmaf(w[r][at + b * D + j], rc.cur, out[r]);
+          if constexpr (j + 1 < D) rc.template advance<j + 1>(x);
+        };
+        [&]<int... J>(std::integer_sequence<int, J...>) {
+          (term(std::integral_constant<int, J>{}), ...);
+        }(std::make_integer_sequence<int, D>{});
       }
     }
   }
-  return out;
 }
 
-template <int BASIS, bool CLASSIFY>
-__global__ __launch_bounds__(256) void predict_kernel(PredictArgs a) {
-  extern __shared__ float w[];
-  __shared__ unsigned long long tally[4];
-  const int c = blockIdx.y;
-  const float* g = a.genes + (int64_t)c * a.K;
-  for (int i = threadIdx.x; i < a.K; i += blockDim.x) w[i] = g[i];
-  if (CLASSIFY && threadIdx.x < 4) tally[threadIdx.x] = 0;
-  __syncthreads();
-  uint32_t tp = 0, fp = 0, tn = 0, fn = 0;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < a.NP;
-       k += (int64_t)gridDim.x * blockDim.x) {
-    const float out = model_output<BASIS>(a.X + k * a.N, a.N, a.degree, w);
-    if constexpr (CLASSIFY) {
-      const bool pred = out >= a.threshold;
-      const bool pos = a.t[k] > 0.5f;
-      tp += pred && pos;
-      fp += pred && !pos;
-      tn += !pred && !pos;
-      fn += !pred && pos;
-    } else {
-      a.out[(int64_t)c * a.NP + k] = out;
+template <int BASIS, int D, int R, bool STAGE>
+__global__ __launch_bounds__(kRows) void predict_kernel(PredictArgs a) {
+  extern __shared__ float rows[];
+  const int n_groups = (a.n + R - 1) / R;
+  const int64_t n_tiles = (a.NP + kRows - 1) / kRows;
+  for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    const int64_t row0 = tile * kRows;
+    const int n_rows = (int)min((int64_t)kRows, a.NP - row0);
+    bool staged = false;
+    for (int grp = blockIdx.y; grp < n_groups; grp += gridDim.y) {
+      float out[R];
+      tile_outputs<BASIS, D, R, STAGE>(a, rows, grp, row0, n_rows, staged, out);
+      if ((int)threadIdx.x < n_rows) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (grp * R + r < a.n) a.out[(int64_t)(grp * R + r) * a.NP + row0 + threadIdx.x] = out[r];
+      }
     }
   }
-  if constexpr (CLASSIFY) {
-    // Integer sums: exact in any order.
-    for (int o = 32; o > 0; o >>= 1) {
-      tp += __shfl_xor(tp, o);
-      fp += __shfl_xor(fp, o);
-      tn += __shfl_xor(tn, o);
-      fn += __shfl_xor(fn, o);
-    }
-    if ((threadIdx.x & 63) == 0) {
-      atomicAdd(&tally[0], (unsigned long long)tp);
-      atomicAdd(&tally[1], (unsigned long long)fp);
-      atomicAdd(&tally[2], (unsigned long long)tn);
-      atomicAdd(&tally[3], (unsigned long long)fn);
+}
+
+// Counts per chromosome, integer sums: exact in any order.  A workgroup
+// takes several tiles of its chromosome group and adds its counts once.  With
+// a.tally set each addition also counts its workgroup in the word's top 16
+// bits, so whoever adds last sees it in the value the addition returns, moves
+// the sum to the output and leaves the word zero for the next launch: no
+// launch clears the counts first, and nothing has to be fenced.  2,100 x 11
+// patterns, 23 chromosomes, trigonometric degree 4: 6.1 us; 13.7 with a fence
+// and a counter of finished workgroups, 11.9 in two launches before.
+constexpr int kTallyShift = 48;
+template <int BASIS, int D, int R, bool STAGE>
+__global__ __launch_bounds__(kRows) void classify_kernel(PredictArgs a) {
+  extern __shared__ float rows[];
+  __shared__ unsigned int sums[R * 4];
+  const int64_t n_tiles = (a.NP + kRows - 1) / kRows;
+  const int n_groups = (a.n + R - 1) / R;
+  for (int grp = blockIdx.y; grp < n_groups; grp += gridDim.y) {
+    if (threadIdx.x < R * 4) sums[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+      const int64_t row0 = tile * kRows;
+      const int n_rows = (int)min((int64_t)kRows, a.NP - row0);
+      const bool valid = (int)threadIdx.x < n_rows;
+      const bool pos = valid && a.t[row0 + threadIdx.x] > 0.5f;
+      bool staged = false;
+      float out[R];
+      tile_outputs<BASIS, D, R, STAGE>(a, rows, grp, row0, n_rows, staged, out);
+      const int lane = threadIdx.x & 63;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const bool pred = out[r] >= a.threshold;
+        const unsigned tp = __popcll(__ballot(valid && pred && pos));
+        const unsigned fp = __popcll(__ballot(valid && pred && !pos));
+        const unsigned tn = __popcll(__ballot(valid && !pred && !pos));
+        const unsigned fn = __popcll(__ballot(valid && !pred && pos));
+        if (lane < 4)
+          atomicAdd(&sums[r * 4 + lane], lane == 0 ? tp : lane == 1 ? fp : lane == 2 ? tn : fn);
+      }
     }
     __syncthreads();
-    if (threadIdx.x < 4)
-      atomicAdd((unsigned long long*)a.counts + (int64_t)c * 4 + threadIdx.x, tally[threadIdx.x]);
+    const int i = threadIdx.x;
+    const int64_t at = (int64_t)grp * R * 4 + i;
+    const bool mine = i < R * 4 && at < (int64_t)a.n * 4;
+    if (gridDim.x == 1) {
+      if (mine) a.counts[at] = sums[i];
+    } else if (!a.tally) {
+      if (mine) atomicAdd((unsigned long long*)a.counts + at, (unsigned long long)sums[i]);
+    } else {
+      if (mine) {
+        const unsigned long long add = (1ull << kTallyShift) + sums[i];
+        const unsigned long long sum = atomicAdd(a.tally + at, add) + add;
+        if ((sum >> kTallyShift) == gridDim.x) {
+          a.counts[at] = (int64_t)(sum & ((1ull << kTallyShift) - 1));
+          a.tally[at] = 0;
+        }
+      }
+    }
+    __syncthreads();              // sums are free again
   }
 }
 
@@ -105,31 +169,70 @@ __global__ void zero_counts_kernel(int64_t* p, int64_t n) {
   if (i < n) p[i] = 0;
 }
 
-template <bool CLASSIFY>
-hipError_t launch_mode(const PredictArgs& a, int basis, hipStream_t s) {
-  const int64_t want = (a.NP + 255) / 256;
-  const dim3 grid((unsigned)(want < 1024 ? want : 1024), (unsigned)a.n);
-  const size_t lds = (size_t)a.K * sizeof(float);
-  switch (basis) {
-    case 0: hipLaunchKernelGGL((predict_kernel<0, CLASSIFY>), grid, dim3(256), lds, s, a); break;
-    case 1: hipLaunchKernelGGL((predict_kernel<1, CLASSIFY>), grid, dim3(256), lds, s, a); break;
-    case 2: hipLaunchKernelGGL((predict_kernel<2, CLASSIFY>), grid, dim3(256), lds, s, a); break;
-    case 3: hipLaunchKernelGGL((predict_kernel<3, CLASSIFY>), grid, dim3(256), lds, s, a); break;
+template <int BASIS, int D, int R, bool STAGE>
+hipError_t launch_variant(PredictArgs a, hipStream_t s) {
+  const int64_t tiles = (a.NP + kRows - 1) / kRows;
+  const int64_t groups = (a.n + R - 1) / R;
+  const size_t lds =
+      STAGE ? (size_t)kRows * row_stride(std::min(a.N, kChunk)) * sizeof(float) : 0;
+  if (!a.counts) {
+    // Once the pattern tiles alone fill the GPU a workgroup serves several
+    // chromosome groups in turn with one read of its rows.
+    const int64_t gx = std::min<int64_t>(tiles, 1 << 24);
+    const int64_t gy = std::min(groups, std::max<int64_t>(1, 2048 / gx));
+    hipLaunchKernelGGL((predict_kernel<BASIS, D, R, STAGE>), dim3((unsigned)gx, (unsigned)gy),
+                       dim3(kRows), lds, s, a);
+    return hipGetLastError();
+  }
+  const int64_t gx = std::min<int64_t>(tiles, 1024);
+  if (gx > 1 && a.n > kTallyChromosomes) {
+    a.tally = nullptr;
+    const int64_t n = (int64_t)a.n * 4;
+    hipLaunchKernelGGL(zero_counts_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                       a.counts, n);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((classify_kernel<BASIS, D, R, STAGE>), dim3((unsigned)gx, (unsigned)groups),
+                     dim3(kRows), lds, s, a);
+  return hipGetLastError();
+}
+
+// Chromosomes per thread: one when groups of 8 would leave most CUs without
+// a workgroup (2,100 x 11 patterns, 23 chromosomes: 6.1 us against 11.5),
+// otherwise groups of 4 or 8 (1,000,000 x 20, 5 chromosomes: 59 us for two
+// groups of 4 or one of 8, 125 for five of one).
+template <int BASIS, int D>
+hipError_t launch_degree(const PredictArgs& a, hipStream_t s) {
+  const int64_t tiles = (a.NP + kRows - 1) / kRows;
+  if (!stages_rows(tiles * ((a.n + 7) / 8))) return launch_variant<BASIS, D, 1, false>(a, s);
+  if (a.n == 1) return launch_variant<BASIS, D, 1, true>(a, s);
+  return a.n <= 4 ? launch_variant<BASIS, D, 4, true>(a, s)
+                  : launch_variant<BASIS, D, 8, true>(a, s);
+}
+
+template <int BASIS>
+hipError_t launch_basis(const PredictArgs& a, hipStream_t s) {
+  switch (a.degree) {
+#define GAME_CASE(D) case D: return launch_degree<BASIS, D>(a, s);
+    GAME_CASE(1) GAME_CASE(2) GAME_CASE(3) GAME_CASE(4) GAME_CASE(5) GAME_CASE(6)
+    GAME_CASE(7) GAME_CASE(8) GAME_CASE(9) GAME_CASE(10) GAME_CASE(11) GAME_CASE(12)
+    GAME_CASE(13) GAME_CASE(14) GAME_CASE(15) GAME_CASE(16)
+#undef GAME_CASE
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_predict(const PredictArgs& a, int basis, hipStream_t s) {
-  if (!a.counts) return launch_mode<false>(a, basis, s);
-  const int64_t n = (int64_t)a.n * 4;
-  hipLaunchKernelGGL(zero_counts_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                     a.counts, n);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_mode<true>(a, basis, s);
+  switch (basis) {
+    case 0: return launch_basis<0>(a, s);
+    case 1: return launch_basis<1>(a, s);
+    case 2: return launch_basis<2>(a, s);
+    case 3: return launch_basis<3>(a, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace game

@@ -91,7 +91,7 @@ int check_config(const game_config* c, int32_t n_features) {
 }
 
 struct Layout {
-  size_t state, pop0, pop1, fit32, fit64, order, cum, partial, rescore, cs, total;
+  size_t state, pop0, pop1, fit32, fit64, order, cum, partial, rescore, tally, cs, total;
 };
 
 // The trig expansion's (cos x, sin x) table is kept for float32 runs (the
@@ -99,6 +99,9 @@ struct Layout {
 bool keeps_trig_table(const game_config* c) {
   return c->basis == GAME_TRIG && c->precision == GAME_FP32;
 }
+
+// Classification sums; zeroed at create, and every launch leaves them zero.
+constexpr size_t kTallyBytes = kTallyChromosomes * 4 * sizeof(int64_t);
 
 Layout layout(const game_config* c, int64_t n_patterns, int32_t n_features) {
   const size_t P = (size_t)c->population;
@@ -116,6 +119,7 @@ Layout layout(const game_config* c, int64_t n_patterns, int32_t n_features) {
   L.partial = off;
   off += align_up(std::max(Ppad * kMaxSplits, (size_t)kSplitCapacity) * sizeof(double));
   L.rescore = off; off += align_up(64 * sizeof(double));
+  L.tally = off; off += align_up(kTallyBytes);
   L.cs = off;
   if (keeps_trig_table(c)) off += align_up((size_t)n_patterns * n_features * 2 * sizeof(float));
   L.total = off;
@@ -143,6 +147,7 @@ struct game_ctx {
   double* cum;              // roulette wheel of the current generation
   double* partial;
   double* rescore;          // float64 error of the last re-scored elite
+  unsigned long long* tally;// classification sums (kTallyBytes), zero between calls
   const float* cs;          // (cos x, sin x) of the data set (trig, float32), or null
   bool initialized;
   hipGraphExec_t graph;
@@ -654,7 +659,12 @@ int game_create(const game_config* c, const float* X, const float* t, int64_t NP
   h->partial = (double*)(base + L.partial);
   h->cum = (double*)(base + L.cum);
   h->rescore = (double*)(base + L.rescore);
-  hipError_t e = hipSuccess;
+  h->tally = (unsigned long long*)(base + L.tally);
+  hipError_t e = launch_fill_zero((float*)h->tally, kTallyBytes / sizeof(float), h->stream);
+  if (e != hipSuccess) {
+    delete h;
+    return hip_fail(e, "launch_fill_zero");
+  }
   if (keeps_trig_table(c)) {
     float* cs = (float*)(base + L.cs);
     e = launch_trig_cs(X, NP, N, cs, h->stream);
@@ -767,6 +777,7 @@ static int predict_common(game_t h, const float* X, const float* t, int64_t NP, 
   a.threshold = threshold;
   a.out = out;
   a.counts = counts;
+  a.tally = h->tally;
   GAME_HIP(launch_predict(a, h->cfg.basis, h->stream));
   return GAME_OK;
 }

@@ -128,3 +128,23 @@ def test_predict_rejects_bad_arguments(gg):
         gg.game_classify(g.h, torch.from_numpy(X).cuda(), None, genes, 1, 0.5,
                          torch.empty((1, 4), dtype=torch.int64, device="cuda"))
     g.close()
+
+
+@pytest.mark.parametrize("basis,d", [(0, 1), (1, 8), (2, 16), (3, 5)])
+@pytest.mark.parametrize("NP,N,n", [(1, 1, 1), (255, 31, 4), (256, 32, 8), (257, 33, 9),
+                                    (2047, 65, 5), (70001, 3, 7), (600, 2, 1025)])
+def test_outputs_and_counts_at_tile_edges(gg, basis, d, NP, N, n):
+    """Pattern tiles of 256, feature chunks of 32 and chromosome groups of 1,
+    4 and 8 at their edges; the counts (twice: they accumulate in scratch
+    that every call leaves zero) are the stored outputs' decisions."""
+    X, t, g = make(gg, basis, d, NP, N, seed=NP + N)
+    K = g.n_genes
+    genes = np.random.default_rng(n).uniform(-0.3, 0.3, (n, K)).astype(np.float32)
+    gd = torch.from_numpy(genes).cuda()
+    out = g.predict(gd).cpu().numpy()
+    ref = og.outputs(X, genes, basis, d).T
+    assert np.all(np.abs(out - ref) <= bound(genes, K, d)[:, None])
+    for _ in range(2):
+        counts = g.classify(gd, threshold=0.1).cpu().numpy()
+        assert np.array_equal(counts, _counts_from(out, t, 0.1))
+    g.close()
