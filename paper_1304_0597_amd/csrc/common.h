@@ -145,6 +145,7 @@ struct PredictArgs {
 constexpr int kTallyChromosomes = 1024;
 hipError_t launch_predict(const PredictArgs& a, int basis, hipStream_t s);
 
+constexpr int kRescoreBlocks = 1024;   // most pattern blocks of a re-score
 struct Rescore64Args {
   const float* X;
   const float* t;

@@ -228,11 +228,10 @@ hipError_t rescore64(const game_ctx* h, const float* X, const float* t, int64_t 
   r.N = h->N;
   r.K = h->K;
   r.n = n;
-  int64_t blocks = (NP + 255) / 256;
-  const int64_t cap = (int64_t)kMaxSplits * kMaxTileCols / (n < 1 ? 1 : n);
-  if (blocks > 256) blocks = 256;
-  if (blocks > cap) blocks = cap;
-  if (blocks < 1) blocks = 1;
+  // One tile of 256 patterns per block up to four blocks per CU, as far as
+  // the partials' room goes.
+  const int64_t blocks =
+      std::min({(NP + 255) / 256, (int64_t)kRescoreBlocks, (int64_t)kSplitCapacity / n});
   r.blocks = (int32_t)blocks;
   r.error_fn = h->cfg.error_fn;
   r.R = h->cfg.tmse_R;

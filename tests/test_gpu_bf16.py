@@ -164,3 +164,17 @@ def test_precision_workload_sampled(gg):
     np.testing.assert_allclose(r64, ref, rtol=1e-10)
     assert np.all(np.abs(f64[idx] - ref) <= bound), np.abs(f64[idx] - ref) / bound
     g.close()
+
+
+@pytest.mark.parametrize("basis,d", [(0, 1), (1, 8), (2, 16), (3, 5)])
+@pytest.mark.parametrize("NP,N,n", [(1, 1, 1), (255, 33, 2), (257, 2, 9), (65537, 31, 1),
+                                    (65600, 33, 2), (66000, 5, 5), (300000, 3, 3)])
+def test_rescore64_at_tile_edges(gg, basis, d, NP, N, n):
+    """Pattern tiles of 256, feature chunks of 32, the 1,024-block limit and
+    chromosome groups of 1, 2 and 4 at their edges."""
+    X, t, W = problem(NP, N, d, max(n, 2), basis, seed=NP + N)
+    g = make_game(gg, X, t, basis, d, max(n, 2), precision=0)
+    got = g.rescore64(torch.from_numpy(W[:n]).cuda()).cpu().numpy()
+    ref = og.fitness(X, t, W[:n], basis, d)
+    g.close()
+    assert np.all(np.abs(got - ref) <= 1e-11 * ref)
