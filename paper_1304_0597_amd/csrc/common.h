@@ -7,6 +7,7 @@
 
 namespace game {
 
+constexpr int kSplitLoads = 8;   // partials of a lane in flight together
 // Sum over splits of chromosome i's partials, called by all 64 lanes of a
 // wave: lane l adds splits l, l+64, ... in order, then a butterfly adds the
 // lane sums.  Partner lanes add the same two values (a + b == b + a), so
@@ -14,7 +15,17 @@ namespace game {
 __device__ __forceinline__ double wave_split_sum(const double* partial, int64_t ld, int n_splits,
                                                  int i) {
   double s = 0.0;
-  for (int k = (int)(threadIdx.x & 63); k < n_splits; k += 64) s += partial[(int64_t)k * ld + i];
+  for (int k0 = (int)(threadIdx.x & 63); k0 < n_splits; k0 += 64 * kSplitLoads) {
+    double v[kSplitLoads];
+#pragma unroll
+    for (int u = 0; u < kSplitLoads; ++u) {
+      const bool in = k0 + 64 * u < n_splits;
+      const double p = partial[in ? (int64_t)(k0 + 64 * u) * ld + i : 0];
+      v[u] = in ? p : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < kSplitLoads; ++u) s += v[u];
+  }
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   return s;
 }

@@ -31,16 +31,23 @@
 //    computed once per data set (FitArgs::cs); otherwise sincosf in every
 //    chromosome tile.
 //  * Wave tile 64 patterns x 32*CB chromosomes: each generated A value feeds
-//    CB MFMAs per row block.  For a single run whose population exceeds 64
-//    a workgroup takes 128 chromosomes (CB = 4) with eight waves, waves 0-3
-//    on the even pattern tiles of its split and 4-7 on the odd ones (two
-//    waves per SIMD, one gene copy per CU, up to 159 K-steps of genes before
-//    they are chunked); otherwise 64 chromosomes (CB = 2) with four waves
-//    and two workgroups per CU (up to 128 K-steps).  The wider tile halves
-//    the recurrence and feature-load work per MFMA.
+//    CB MFMAs per row block.  CB = 4: a workgroup takes 128 chromosomes with
+//    eight waves, waves 0-3 on the even pattern tiles of its split and 4-7 on
+//    the odd ones (two waves per SIMD, one gene copy per CU, up to 159 K-steps
+//    of genes before they are chunked).  CB = 2 or 1: 64 or 32 chromosomes with
+//    four waves, several workgroups per CU (up to 128 K-steps).  Wider tiles
+//    spread the recurrence and the feature loads over more MFMAs, narrower
+//    ones fill the GPU when there are few tiles; plan_fitness chooses.
+//  * At low degree a feature pair is little work next to its load's latency:
+//    the features of several pairs, and the targets, are loaded a group (a
+//    tile) ahead, and rows of whole 16-byte quads a quad per lane and load.
+//    7,168,000 x 16 patterns, degree 1, 23 chromosomes (TMSE): 347 us before,
+//    172 now (2.8 TB/s; MFMAs and epilogue take about half of it).
 //  * Grid: (pattern split) x (chromosome tile); consecutive blocks of one
 //    split are mapped onto one XCD so its L2 serves the split's rows to all
 //    chromosome tiles.
+#include <algorithm>
+
 #include "fitness_f32_body.h"
 
 namespace game {
@@ -48,6 +55,8 @@ namespace game {
 template <int BASIS, int D, int CB>
 __global__ __launch_bounds__(64 * fit_waves(CB), 8 / fit_waves(CB)) void fitness_f32_kernel(FitArgs a) {
   extern __shared__ float lds[];
+  const int total = a.n_ctiles * a.n_splits;
+  const int b = blockIdx.x;
   if (a.stop) {
     const int32_t stopped = *a.stop;
     if (a.stop_seen && blockIdx.x == 0 && threadIdx.x == 0) *a.stop_seen = stopped;
@@ -55,9 +64,10 @@ __global__ __launch_bounds__(64 * fit_waves(CB), 8 / fit_waves(CB)) void fitness
   }
   const float* __restrict__ genes = a.genes;
   if (a.gen_sel && (*a.gen_sel & 1)) genes = a.genes_alt;
-  const int total = gridDim.x;
-  const int b = blockIdx.x;
-  const int L = a.xcd_remap ? (b & 7) * (total >> 3) + (b >> 3) : b;
+  // Consecutive L on one XCD (workgroup b runs on XCD b % 8), the first
+  // total % 8 XCDs taking one more.
+  const int xcd = b & 7;
+  const int L = xcd * (total >> 3) + min(xcd, total & 7) + (b >> 3);
   const int split = L / a.n_ctiles;
   const int ctile = L - split * a.n_ctiles;
   fitness_f32_block<BASIS, D, CB>(a, genes, split, ctile, lds);
@@ -66,20 +76,21 @@ __global__ __launch_bounds__(64 * fit_waves(CB), 8 / fit_waves(CB)) void fitness
 template <int BASIS, int D, int CB>
 static hipError_t launch_cb(const FitArgs& a, hipStream_t s) {
   const size_t lds = fitness_lds_bytes(a, D);
+  const int threads = 64 * fit_waves(CB);
   const int grid = a.n_ctiles * a.n_splits;
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute((const void*)fitness_f32_kernel<BASIS, D, CB>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((fitness_f32_kernel<BASIS, D, CB>), dim3(grid), dim3(64 * fit_waves(CB)), lds,
-                     s, a);
+  hipLaunchKernelGGL((fitness_f32_kernel<BASIS, D, CB>), dim3(grid), dim3(threads), lds, s, a);
   return hipGetLastError();
 }
 
 template <int BASIS, int D>
 static hipError_t launch_one(const FitArgs& a, hipStream_t s) {
   if (a.tile_cols == 128) return launch_cb<BASIS, D, 4>(a, s);
+  if (a.tile_cols == 32) return launch_cb<BASIS, D, 1>(a, s);
   return launch_cb<BASIS, D, 2>(a, s);
 }
 
@@ -106,39 +117,84 @@ hipError_t launch_fitness_f32(const FitArgs& a, int basis, int degree, hipStream
 }
 
 size_t fitness_lds_bytes(const FitArgs& a, int degree) {
-  const int cols = a.tile_cols == 128 ? 128 : kTileCols;
+  const int cols = a.tile_cols;
   const size_t w = (size_t)(a.n_chunks > 1 ? 2 : 1) * cols *
                    (2 * a.pairs_per_chunk * degree + 1) * sizeof(float);
   const size_t red = (size_t)fit_waves(cols / 32) * cols * sizeof(double);
   return w > red ? w : red;
 }
 
+// K-steps (per lane half) of genes that stay in LDS for the whole launch:
+// several narrow workgroups share a CU, a 128-chromosome one has it to itself;
+// beyond that the genes pass through two buffers in chunks.
+static int max_staged_steps(int cb) { return cb == 4 ? kMaxWideSteps : kMaxChunkSteps; }
+
+// Estimated time of a step (64 rows x 32 cb chromosomes) of w waves per SIMD,
+// in cycles of the SIMD per wave.  The MFMAs take m; the rest (recurrence,
+// feature and gene reads, epilogue) costs v beyond them at two or more waves
+// per SIMD and twice that when nothing runs beside it; genes that pass through
+// LDS in chunks cost the more the narrower the tile.  Fitted to launches of 16
+// to 320 expansion terms and 23 to 2,048 chromosomes (within 5 % of their
+// times, for 64-chromosome tiles within 15).
+static int64_t step_cost(int cb, int ksteps, int w) {
+  const int64_t m = 128 * cb * (ksteps + 1);
+  int64_t v = cb == 4 ? 4200 + 40 * ksteps : cb == 2 ? 3400 + 40 * ksteps : 1800 + 17 * ksteps;
+  if (ksteps > max_staged_steps(cb)) v += m * (cb == 4 ? 13 : cb == 2 ? 40 : 55) / 100;
+  return m + (w > 1 ? v : 2 * v);
+}
+
 void plan_fitness(FitArgs& a, int degree, int basis, bool wide) {
   a.U = (basis == 3 ? 2 : 1) * a.N;
   a.Q = (a.U + 1) / 2;
-  a.tile_cols = wide && a.n_chrom > kTileCols ? 128 : kTileCols;
-  // K-steps (per lane half) of genes that stay in LDS for the whole launch:
-  // two 64-chromosome workgroups share a CU, a 128-chromosome one has it to
-  // itself; beyond that the genes pass through two buffers in chunks.
-  const int max_steps = a.tile_cols == 128 ? kMaxWideSteps : kMaxChunkSteps;
-  int ppc = a.Q * degree <= max_steps ? a.Q : kChunkSteps / degree;
+  a.n_tiles = (int32_t)((a.NP + kTileRows - 1) / kTileRows);
+  // Tile width and splits of a single run: the combination of least estimated
+  // time.  Wide tiles do the least work besides MFMAs, but a launch has few of
+  // them: 4,000 x 20 patterns, Legendre 8, 100 chromosomes take 31 us in 16
+  // workgroups of 128 chromosomes and 13 in 64 of 32; 200,000 x 20 with 2,048
+  // take 980 in 128s, 1,046 in 64s and 1,091 in 32s.  All workgroups of a
+  // launch are resident at once (one of eight waves per CU, two or four of four
+  // waves): splits are rounded down to that, since a few workgroups more run a
+  // round of their own (100,000 x 32, Chebyshev 10, 1,500 chromosomes: 1,615 us
+  // in 264 workgroups, 850 in 252).
+  int best_cb = 2, best_tps = 1;
+  int64_t best = INT64_MAX;
+  for (int cb = 4; cb >= 1; cb >>= 1) {
+    if (!wide && cb != 2) continue;
+    if (cb > 1 && 32 * (cb / 2) >= a.n_chrom && wide) continue;   // half the tile would be empty
+    const int ctiles = (a.n_chrom + 32 * cb - 1) / (32 * cb);
+    const int streams = cb == 4 ? 2 : 1;
+    // As many workgroups per CU as fit (few terms need the most reads in
+    // flight), or fewer when that saves more than 3 %.
+    const int most = cb == 4 ? 1 : cb == 2 ? 2 : a.Q * degree <= 16 ? 8 : 4;
+    int64_t best_of_cb = INT64_MAX;
+    int tps_of_cb = 1;
+    for (int per_cu = most; per_cu >= 1; --per_cu) {
+      int splits = 256 * per_cu / ctiles;
+      splits = std::min({std::max(splits, 1), max_splits(ctiles * 32 * cb), a.n_tiles});
+      const int tps = (a.n_tiles + splits - 1) / splits;
+      const int64_t groups = (int64_t)ctiles * ((a.n_tiles + tps - 1) / tps);
+      const int64_t w = (groups + 255) / 256 * std::min(streams, tps);
+      const int64_t cost = w * ((tps + streams - 1) / streams) * step_cost(cb, a.Q * degree, (int)w);
+      if (best_of_cb == INT64_MAX || cost + cost / 32 < best_of_cb) {
+        best_of_cb = cost;
+        tps_of_cb = tps;
+      }
+    }
+    if (best_of_cb < best) {
+      best = best_of_cb;
+      best_cb = cb;
+      best_tps = tps_of_cb;
+    }
+  }
+  a.tile_cols = 32 * best_cb;
+  a.tiles_per_split = best_tps;
+  a.n_splits = (a.n_tiles + best_tps - 1) / best_tps;
+  a.n_ctiles = (a.n_chrom + a.tile_cols - 1) / a.tile_cols;
+  a.ld_partial = a.n_ctiles * a.tile_cols;
+  int ppc = a.Q * degree <= max_staged_steps(best_cb) ? a.Q : kChunkSteps / degree;
   if (ppc < 1) ppc = 1;
   a.pairs_per_chunk = ppc;
   a.n_chunks = (a.Q + ppc - 1) / ppc;
-  a.n_ctiles = (a.n_chrom + a.tile_cols - 1) / a.tile_cols;
-  a.ld_partial = a.n_ctiles * a.tile_cols;
-  a.n_tiles = (int32_t)((a.NP + kTileRows - 1) / kTileRows);
-  // Aim at all resident workgroups on 256 CUs in one wave of blocks: one
-  // eight-wave workgroup per CU for 128-chromosome tiles, two four-wave ones
-  // for 64-chromosome tiles.
-  const int target = a.tile_cols == 128 ? 256 : 512;
-  int splits = (target + a.n_ctiles - 1) / a.n_ctiles;
-  if (splits > max_splits(a.ld_partial)) splits = max_splits(a.ld_partial);
-  if (splits > a.n_tiles) splits = a.n_tiles;
-  if (splits < 1) splits = 1;
-  a.tiles_per_split = (a.n_tiles + splits - 1) / splits;
-  a.n_splits = (a.n_tiles + a.tiles_per_split - 1) / a.tiles_per_split;
-  a.xcd_remap = ((a.n_ctiles * a.n_splits) % 8) == 0 ? 1 : 0;
 }
 
 // fitness[i] = sum_s partial[s][i] / NP (wave_split_sum order), RMSE takes

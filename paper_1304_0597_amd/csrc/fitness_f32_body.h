@@ -60,6 +60,21 @@ __device__ __forceinline__ gptr_f32 global_f32(const float* p) { return (gptr_f3
 // take the even row tiles of the split and 4-7 the odd ones, two per SIMD).
 __host__ __device__ constexpr int fit_waves(int cb) { return cb == 4 ? 8 : 4; }
 
+// lo = (a's lower half, b's lower half), hi = (a's upper, b's upper).
+__device__ __forceinline__ void swap_halves(float a, float b, float& lo, float& hi) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                  false);
+  lo = __uint_as_float(r[0]);
+  hi = __uint_as_float(r[1]);
+}
+
+// Feature pairs whose loads are issued together, a group ahead of their use.
+// A pair of degree d is 2 d CB MFMAs of work; at low degree that is far less
+// than a load's latency.
+__host__ __device__ constexpr int pairs_ahead(int d, int cb) {
+  return cb == 4 ? (d <= 2 ? 4 : d == 4 ? 2 : 1) : (d == 1 ? 8 : d <= 4 ? 4 : d <= 8 ? 2 : 1);
+}
+
 // Tile range [split's tiles] x chromosome tile ctile (32*CB chromosomes,
 // the first one ctile * 32*CB) of the launch described by a_in; writes
 // a.partial[split * ld_partial + chromosome].  Each wave takes RB/2 consecutive 256-row tiles at a time
@@ -107,6 +122,7 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
   constexpr int TPW = RB / 2;         // consecutive row tiles per wave
   constexpr int STEP = TS * TPW;      // row tiles per step of the workgroup
   constexpr int kCols = 32 * CB;      // chromosomes per tile
+  constexpr int QP = RB == 2 ? pairs_ahead(D, CB) : 1;   // feature pairs loaded at a time
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int wq = wave & 3;            // 64-row slice of a tile
@@ -159,12 +175,6 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
     }
   };
 
-  if (a.n_chunks == 1) {
-    stage_issue(0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's copies landed
-    __syncthreads();
-  }
-
   double acc64[CB];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) acc64[cb] = 0.0;
@@ -180,34 +190,97 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
   auto row_of = [&](int tile, int rb) -> int64_t {
     return (int64_t)(tile + rb / 2) * kTileRows + wq * 64 + (rb & 1) * 32 + m;
   };
-  auto load_x = [&](int tile, int q, float (&xo)[RB], float (&so)[RB]) {
+  // Rows of whole 16-byte quads are read a quad per lane and load (low degrees,
+  // whose feature reads would otherwise outnumber the MFMAs): a load of single
+  // features moves 8 bytes of each row's 64-byte line.
+  constexpr bool kQuads = !trig && QP >= 4;
+  const bool quads = kQuads && N % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0 &&
+                     (a.n_chunks == 1 || ppc % 4 == 0);
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef const f32x4 __attribute__((address_space(1)))* gptr_f32x4;
+  // Features of pairs q0 .. q0 + n - 1 (n <= QP) of the wave's rows.
+  auto load_x = [&](int tile, int q0, int n, float (&xo)[QP][RB], float (&so)[QP][RB]) {
     if constexpr (kTable) {
       typedef float f32x2 __attribute__((ext_vector_type(2)));
       typedef const f32x2 __attribute__((address_space(1)))* gptr_f32x2;
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
         const int64_t r = row_of(tile, rb);
-        f32x2 v = {0.f, 0.f};
-        if (r < NP) v = ((gptr_f32x2)a.cs)[r * N + q];
-        xo[rb] = v.x;
-        so[rb] = v.y;
+        gptr_f32x2 src = (gptr_f32x2)a.cs + r * N + q0;
+#pragma unroll
+        for (int i = 0; i < QP; ++i) {
+          f32x2 v = {0.f, 0.f};
+          if (r < NP && (i == 0 || i < n)) v = src[i];
+          xo[i][rb] = v.x;
+          so[i][rb] = v.y;
+        }
       }
       return;
     }
-    const int u = 2 * q + h;
-    const int f = trig ? q : u;
-    const bool fvalid = trig ? true : (u < a.U);
+    if constexpr (kQuads) {
+      if (quads) {
+        // Half h reads the quad 2 q0 + 8 k + 4 h .. + 3 of its row; unpack_x
+        // exchanges the halves' words.
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          const int64_t r = row_of(tile, rb);
+          const int f = 2 * q0 + 4 * h;
+          gptr_f32x4 src = (gptr_f32x4)(global_f32(a.X) + r * N + f);
+#pragma unroll
+          for (int k = 0; k < QP / 4; ++k) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (r < NP && 4 * k < n && f + 8 * k < N) v = src[2 * k];
+            xo[4 * k][rb] = v.x;
+            xo[4 * k + 1][rb] = v.y;
+            xo[4 * k + 2][rb] = v.z;
+            xo[4 * k + 3][rb] = v.w;
+          }
+        }
+        return;
+      }
+    }
+    const int f0 = trig ? q0 : 2 * q0 + h;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const int64_t r = row_of(tile, rb);
-      xo[rb] = (r < NP && fvalid) ? global_f32(a.X)[r * N + f] : 0.f;
+      gptr_f32 src = global_f32(a.X) + r * N + f0;
+#pragma unroll
+      for (int i = 0; i < QP; ++i) {
+        const int off = trig ? i : 2 * i;
+        // the odd half of the last pair may lie past the sub-features
+        const bool in = (i == 0 || i < n) && (trig || f0 + off < a.U);
+        xo[i][rb] = (r < NP && in) ? src[off] : 0.f;
+      }
     }
   };
 
-  float xn[RB], sn[RB];
+  float xn[QP][RB], sn[QP][RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) xn[rb] = sn[rb] = 0.f;
-  if (tile_begin + wg * TPW < tile_end) load_x(tile_begin + wg * TPW, 0, xn, sn);
+  for (int i = 0; i < QP; ++i)
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) xn[i][rb] = sn[i][rb] = 0.f;
+  // Minus the targets of the wave's rows (0 past the data); at low degree
+  // they are read a tile ahead too.
+  constexpr bool kTargetsAhead = QP >= 4;
+  float tn[RB];
+  auto load_t = [&](int tile, float (&to)[RB]) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int64_t r = row_of(tile, rb);
+      to[rb] = (RB == 2 || tile + rb / 2 < tile_end) && r < NP ? -global_f32(a.t)[r] : 0.f;
+    }
+  };
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) tn[rb] = 0.f;
+  if (kTargetsAhead && tile_begin + wg * TPW < tile_end) load_t(tile_begin + wg * TPW, tn);
+  const int first_n = min(QP, min(ppc, a.Q));   // pairs of a tile's first group
+  if (tile_begin + wg * TPW < tile_end) load_x(tile_begin + wg * TPW, 0, first_n, xn, sn);
+  if (a.n_chunks == 1) {
+    stage_issue(0, 0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's copies landed
+    __syncthreads();
+  }
+
   // Chunked genes: stage index st runs over (tile, chunk) in loop order and
   // uses buffer st & 1.
   int st = 0;
@@ -229,14 +302,17 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
       row_ok[rb] = (RB == 2 || tile + rb / 2 < tile_end) && row_of(tile, rb) < NP;
-    // Minus the targets of this lane's rows (0 past the data); they join
-    // with the bias in a last K-step, so the load's latency hides behind the
-    // K loop.
+    // The targets join with the bias in a last K-step, so their load's latency
+    // hides behind the K loop.
     float nt[RB];
+    if constexpr (kTargetsAhead) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int64_t r = row_of(tile, rb);
-      nt[rb] = active && row_ok[rb] ? -global_f32(a.t)[r] : 0.f;
+      for (int rb = 0; rb < RB; ++rb) nt[rb] = tn[rb];
+      if (tile + STEP < tile_end) load_t(tile + STEP, tn);
+    } else {
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) nt[rb] = 0.f;
+      if (active) load_t(tile, nt);
     }
     // Accumulators start at zero (an inline constant, nothing to keep live
     // across tiles).
@@ -261,49 +337,69 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
       if (!active) continue;
       const int q_begin = chunk * ppc;
       const int q_end = min(q_begin + ppc, a.Q);
-      for (int q = q_begin; q < q_end; ++q) {
-        float x[RB], sx[RB];
+      for (int q0 = q_begin; q0 < q_end; q0 += QP) {
+        float x[QP][RB], sx[QP][RB];
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          x[rb] = xn[rb];
-          sx[rb] = sn[rb];
-        }
-        // prefetch the next pair, or the first pair of the next tile
-        if (q + 1 < a.Q) load_x(tile, q + 1, xn, sn);
-        else if (tile + STEP < tile_end) load_x(tile + STEP, 0, xn, sn);
-        Recur<FAM> rc[RB];
+        for (int i = 0; i < QP; ++i)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          if constexpr (kTable) {
-            rc[rb].seed_cs(x[rb], sx[rb], h);
-          } else {
-            rc[rb].seed(x[rb], h);
+          for (int rb = 0; rb < RB; ++rb) {
+            x[i][rb] = xn[i][rb];
+            sx[i][rb] = sn[i][rb];
           }
-          zero_chain(rc[rb], row_ok[rb]);
+        if constexpr (kQuads) {
+          if (quads) {
+            // Words 0..3 of a quad pair are features 0..3 in half 0 and 4..7
+            // in half 1; pair i wants features 2 i + h.
+#pragma unroll
+            for (int k = 0; k < QP; k += 4)
+#pragma unroll
+              for (int rb = 0; rb < RB; ++rb) {
+                swap_halves(xn[k][rb], xn[k + 1][rb], x[k][rb], x[k + 2][rb]);
+                swap_halves(xn[k + 2][rb], xn[k + 3][rb], x[k + 1][rb], x[k + 3][rb]);
+              }
+          }
         }
-        const float* wl = wbuf + m * WS + (2 * (q - q_begin) + h) * Dv;
-        // One K-step per degree: CB MFMA columns x two row blocks, then the
-        // recurrence moves every lane's A value to the next degree.
-        auto kstep = [&](auto jc) {
-          constexpr int j = decltype(jc)::value;
-          float b[CB];
+        // prefetch the next group, or the first one of the next tile
+        const int nq = min(q0 + QP, q_end);
+        if (nq < a.Q) load_x(tile, nq, min(QP, (nq < q_end ? q_end : min(nq + ppc, a.Q)) - nq), xn, sn);
+        else if (tile + STEP < tile_end) load_x(tile + STEP, 0, first_n, xn, sn);
 #pragma unroll
-          for (int cb = 0; cb < CB; ++cb) b[cb] = wl[cb * 32 * WS + j];
+        for (int i = 0; i < QP; ++i) {
+          if (i > 0 && q0 + i >= q_end) break;
+          Recur<FAM> rc[RB];
 #pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-              acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(rc[rb].cur, b[cb], acc[rb][cb], 0, 0, 0);
-          if constexpr (j + 1 < D) {
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-              rc[rb].template advance<j + 1>(x[rb]);
+          for (int rb = 0; rb < RB; ++rb) {
+            if constexpr (kTable) {
+              rc[rb].seed_cs(x[i][rb], sx[i][rb], h);
+            } else {
+              rc[rb].seed(x[i][rb], h);
             }
+            zero_chain(rc[rb], row_ok[rb]);
           }
-        };
-        [&]<int... J>(std::integer_sequence<int, J...>) {
-          (kstep(std::integral_constant<int, J>{}), ...);
-        }(std::make_integer_sequence<int, D>{});
+          const float* wl = wbuf + m * WS + (2 * (q0 + i - q_begin) + h) * Dv;
+          // One K-step per degree: CB MFMA columns x RB row blocks, then the
+          // recurrence moves every lane's A value to the next degree.
+          auto kstep = [&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            float b[CB];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) b[cb] = wl[cb * 32 * WS + j];
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+              for (int cb = 0; cb < CB; ++cb)
+                acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(rc[rb].cur, b[cb], acc[rb][cb], 0, 0, 0);
+            if constexpr (j + 1 < D) {
+#pragma unroll
+              for (int rb = 0; rb < RB; ++rb) {
+                rc[rb].template advance<j + 1>(x[i][rb]);
+              }
+            }
+          };
+          [&]<int... J>(std::integer_sequence<int, J...>) {
+            (kstep(std::integral_constant<int, J>{}), ...);
+          }(std::make_integer_sequence<int, D>{});
+        }
       }
     }
 

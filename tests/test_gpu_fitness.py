@@ -261,3 +261,30 @@ def test_trig_table_gives_the_kernels_own_bits(gg, shape):
                           f_pop.cpu().numpy().astype(np.float32).view(np.uint32))
     g2.close()
     batch.close()
+
+
+@pytest.mark.parametrize("basis", [0, 1, 2, 3])
+@pytest.mark.parametrize("shape", [
+    # NP, N, d, P: 32-, 64- and 128-chromosome tiles; feature quads whole and
+    # with a half-filled last group, rows that are no whole quads; genes in
+    # chunks under narrow tiles, of whole quads and not
+    (7001, 16, 1, 23), (7001, 12, 2, 40), (5000, 20, 3, 33), (5000, 24, 4, 65), (3000, 6, 4, 20),
+    (2000, 40, 8, 30), (2000, 300, 2, 20), (1000, 120, 3, 30), (60000, 8, 2, 64),
+    (300, 4, 1, 1500)], ids=lambda s: "x".join(map(str, s)))
+def test_tile_widths_and_feature_quads(gg, basis, shape):
+    """Errors against the oracle, and the same bits from an X that starts 4
+    bytes past a 16-byte boundary (features then read one by one)."""
+    NP, N, d, P = shape
+    X, t, W = problem(NP, N, d, P, basis, seed=NP + N + d + P)
+    f32, f64 = gpu_fitness(gg, basis, d, X, t, W)
+    ok = within(f64, og.fitness(X, t, W, basis, d), t)
+    assert ok.all(), np.argwhere(~ok)[:5]
+    flat = torch.empty(NP * N + 1, device="cuda")
+    flat[1:] = torch.from_numpy(X).reshape(-1).cuda()
+    Xs = flat[1:].view(NP, N)
+    assert Xs.data_ptr() % 16 == 4
+    cfg = gg.config(basis=basis, degree=d, population=P)
+    g = gg.Game(cfg, Xs, torch.from_numpy(t).cuda())
+    _, s64 = g.fitness(torch.from_numpy(W).cuda(), with64=True)
+    assert np.array_equal(s64.cpu().numpy(), f64)
+    g.close()
