@@ -79,7 +79,24 @@ struct RunState {
   double target;        // stop when best_err <= target
   int32_t evaluated;    // generation of the last evaluation, -1 if none
   int32_t stop_seen;    // stop flag as the generation's fitness launch saw it
-  int32_t pad[6];
+  int32_t gen_seen;     // generation counter as that launch saw it (compact tail)
+  int32_t pad[5];
+};
+
+// Draws of a genetic step made by extra workgroups of the generation's
+// fitness launch (see make_draw); n_items 0: none.
+struct DrawArgs {
+  uint64_t seed;
+  uint64_t thr_mut;
+  float sigma;
+  int32_t K, E;
+  int32_t P;
+  int32_t n_pairs;
+  int32_t blocks;           // Philox blocks of selection words per pair
+  uint64_t* words;          // [n_pairs x blocks x 4]
+  float* mut;               // [P x K]
+  float* cur;               // [P x K] copy of the population being evaluated
+  int32_t n_items;
 };
 
 // Problem view for the fitness kernels.
@@ -91,6 +108,7 @@ struct FitArgs {
   const int32_t* gen_sel;   // when set, genes_alt is used if (*gen_sel & 1)
   const int32_t* stop;      // when set and nonzero the kernel returns
   int32_t* stop_seen;       // when set, block 0 records *stop here
+  int32_t* gen_seen;        // when set, block 0 records *gen_sel here
   double* partial;          // [n_splits x ld_partial] float64 SSE partials
   int64_t NP;
   int32_t N;
@@ -112,6 +130,7 @@ struct FitArgs {
   int32_t basis;            // expansion family (the kernels take it as a template parameter)
   const float* cs;          // trig only: [NP x N] pairs (cos x, sin x) of X, or null
   int32_t tile_cols;        // chromosomes per FP32 tile: 64, or 128 (genes in one chunk)
+  DrawArgs draw;            // float32 launches only
 };
 
 // Fitness-kernel variant of the trigonometric expansion that reads the
@@ -225,10 +244,29 @@ hipError_t launch_finish_rank(const RankArgs& a, hipStream_t s);
 // fit64/fit32 of every chromosome from the split partials (one wave per
 // chromosome, wave_split_sum order); runs before finish_rank.
 hipError_t launch_reduce_fitness(const RankArgs& a, hipStream_t s);
+hipError_t launch_reduce_few(const RankArgs& a, hipStream_t s);
 constexpr int kRankThreads = 1024;
 constexpr int kRankPerBlock = 64;
+// The tail of a small run's generation in one launch (see compact_tail_kernel).
+struct CompactArgs {
+  RankArgs rank;
+  GAArgs ga;
+  const uint64_t* words;    // the generation's draws (DrawArgs)
+  const float* mut;
+  const float* cur;
+  float* live;              // when set, the next population is also written here
+  int32_t blocks;
+  int32_t reduced;          // errors are in rank.fit64 already (many splits)
+  int32_t need_order;       // set by the launch
+  int32_t pair_at;          // set by the launch
+};
+bool compact_fits(int P, int K, int k, int selection);
+int compact_blocks(int k, int selection);
+hipError_t launch_compact_tail(CompactArgs a, hipStream_t s);
+// With zero set, also clears n_zero words there.
 hipError_t launch_set_state(RunState* st, int32_t gen, int32_t max_gen, double target,
-                            int32_t reset, hipStream_t s);
+                            int32_t reset, hipStream_t s, unsigned long long* zero = nullptr,
+                            int32_t n_zero = 0);
 
 // ---------------------------------------------------------------- batches
 // One run of a batch: its data, its fitness plan (float32 kernel geometry),

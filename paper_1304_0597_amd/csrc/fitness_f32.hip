@@ -49,6 +49,7 @@
 #include <algorithm>
 
 #include "fitness_f32_body.h"
+#include "philox.h"
 
 namespace game {
 
@@ -57,27 +58,37 @@ __global__ __launch_bounds__(64 * fit_waves(CB), 8 / fit_waves(CB)) void fitness
   extern __shared__ float lds[];
   const int total = a.n_ctiles * a.n_splits;
   const int b = blockIdx.x;
-  if (a.stop) {
-    const int32_t stopped = *a.stop;
-    if (a.stop_seen && blockIdx.x == 0 && threadIdx.x == 0) *a.stop_seen = stopped;
-    if (stopped) return;
-  }
   const float* __restrict__ genes = a.genes;
-  if (a.gen_sel && (*a.gen_sel & 1)) genes = a.genes_alt;
+  if (a.genes_alt) {
+    if (*a.gen_sel & 1) genes = a.genes_alt;
+    // Kept a branch: a population at a fixed place is staged without waiting
+    // for the generation counter.
+    __asm__ __volatile__("" : "+s"(genes));
+  }
+  if (b >= total) {
+    // The genetic step's draws, on CUs that a small launch leaves idle.
+    const int i = (b - total) * (int)blockDim.x + (int)threadIdx.x;
+    if (!*a.stop && i < a.draw.n_items) make_draw(a.draw, genes, *a.gen_sel + 1, i);
+    return;
+  }
   // Consecutive L on one XCD (workgroup b runs on XCD b % 8), the first
   // total % 8 XCDs taking one more.
   const int xcd = b & 7;
   const int L = xcd * (total >> 3) + min(xcd, total & 7) + (b >> 3);
   const int split = L / a.n_ctiles;
   const int ctile = L - split * a.n_ctiles;
-  fitness_f32_block<BASIS, D, CB>(a, genes, split, ctile, lds);
+  fitness_f32_block<BASIS, D, CB>(a, genes, split, ctile, lds, a.stop);
+  if (b == 0 && threadIdx.x == 0) {
+    if (a.stop_seen) *a.stop_seen = *a.stop;
+    if (a.gen_seen) *a.gen_seen = *a.gen_sel;
+  }
 }
 
 template <int BASIS, int D, int CB>
 static hipError_t launch_cb(const FitArgs& a, hipStream_t s) {
   const size_t lds = fitness_lds_bytes(a, D);
   const int threads = 64 * fit_waves(CB);
-  const int grid = a.n_ctiles * a.n_splits;
+  const int grid = a.n_ctiles * a.n_splits + (a.draw.n_items + threads - 1) / threads;
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute((const void*)fitness_f32_kernel<BASIS, D, CB>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

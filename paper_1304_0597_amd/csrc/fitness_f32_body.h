@@ -79,12 +79,16 @@ __host__ __device__ constexpr int pairs_ahead(int d, int cb) {
 // the first one ctile * 32*CB) of the launch described by a_in; writes
 // a.partial[split * ld_partial + chromosome].  Each wave takes RB/2 consecutive 256-row tiles at a time
 // (its 64-row slice of each: RB 32-row blocks).  genes: the chromosomes
-// being scored; lds: the workgroup's dynamic LDS.  D is the degree.  BASIS
+// being scored; lds: the workgroup's dynamic LDS; stop: when set and nonzero
+// nothing is computed.  D is the degree.  BASIS
 // is the expansion family (kTrigTable: the trigonometric one seeded from
 // the stored (cos x, sin x) table a_in.cs instead of sincosf in every tile).
 template <int BASIS, int D, int CB = 2, int RB = 2>
 __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const float* __restrict__ genes,
-                                                  int split, int ctile, float* lds) {
+                                                  int split, int ctile, float* lds,
+                                                  const int32_t* stop = nullptr) {
+  // Read here, tested once the first copies are on their way.
+  const int32_t stopped = stop ? *stop : 0;
   // The parameters the body uses, read once into scalar registers (so that
   // no store in the loops can be taken to alias them and force reloads).
   FitArgs a;

@@ -17,50 +17,9 @@
 // u32 < floor(p 2^32).  Float steps are single IEEE round-to-nearest
 // operations (this file is built with -ffp-contract=off, and the mutation
 // uses explicit __fmul_rn / __fadd_rn), so results are bit-reproducible.
-#include "common.h"
+#include "philox.h"
 
 namespace game {
-
-struct U64x4 {
-  uint64_t o0, o1, o2, o3;
-};
-
-__device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3,
-                                               uint64_t k0, uint64_t k1) {
-  constexpr uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
-  constexpr uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r) {
-      k0 += W0;
-      k1 += W1;
-    }
-    const uint64_t lo0 = M0 * c0, hi0 = __umul64hi(M0, c0);
-    const uint64_t lo1 = M1 * c2, hi1 = __umul64hi(M1, c2);
-    const uint64_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-    c0 = n0;
-    c1 = lo1;
-    c2 = n2;
-    c3 = lo0;
-  }
-  return {c0, c1, c2, c3};
-}
-
-__device__ __forceinline__ U64x4 draw(uint64_t seed, uint64_t stream, uint64_t gen, uint64_t unit,
-                                      uint64_t blk) {
-  return philox4x64_10(gen, unit, blk, 0, seed, stream);
-}
-
-__device__ __forceinline__ float gauss12(const U64x4& b) {
-  int32_t s = 0;
-#pragma unroll
-  for (int f = 0; f < 4; ++f) {
-    s += (int32_t)((b.o1 >> (16 * f)) & 0xFFFF);
-    s += (int32_t)((b.o2 >> (16 * f)) & 0xFFFF);
-    s += (int32_t)((b.o3 >> (16 * f)) & 0xFFFF);
-  }
-  return (float)(s - 393210) * 0x1p-16f;  // both steps exact
-}
 
 __device__ __forceinline__ float clamp_unit(float v) {
   return v < -1.f ? -1.f : (v > 1.f ? 1.f : v);
@@ -243,6 +202,25 @@ hipError_t launch_reduce_fitness(const RankArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The same errors for a few chromosomes over many splits: a wave per
+// chromosome, each in a workgroup of its own, so that their loads go out from
+// as many CUs (23 chromosomes over 2,000 splits: one workgroup took 28 us).
+__global__ __launch_bounds__(64) void reduce_few_kernel(RankArgs a) {
+  if (a.state->stop_seen) return;
+  const int i = blockIdx.x;
+  const double v = error_from_sum(wave_split_sum(a.partial, a.ld_partial, a.n_splits, i), a.NP,
+                                  a.error_fn);
+  if (threadIdx.x == 0) {
+    a.fit64[i] = v;
+    a.fit32[i] = (float)v;
+  }
+}
+
+hipError_t launch_reduce_few(const RankArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(reduce_few_kernel, dim3(a.P), dim3(64), 0, s, a);
+  return hipGetLastError();
+}
+
 // Evaluation epilogue of one generation: rank order of the errors that
 // reduce_fitness wrote, best chromosome, stop test and the generation
 // counter.  The stop flag that
@@ -294,7 +272,9 @@ hipError_t launch_finish_rank(const RankArgs& a, hipStream_t s) {
 // clears and the generation counter advances, as the stop test does when no
 // criterion holds (the caller has checked that none does).
 __global__ void set_state_kernel(RunState* st, int32_t gen, int32_t max_gen, double target,
-                                 int32_t reset) {
+                                 int32_t reset, unsigned long long* zero, int32_t n_zero) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x)
+    zero[i] = 0;
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   if (reset == 2) {
     st->stop = 0;
@@ -314,8 +294,10 @@ __global__ void set_state_kernel(RunState* st, int32_t gen, int32_t max_gen, dou
 }
 
 hipError_t launch_set_state(RunState* st, int32_t gen, int32_t max_gen, double target,
-                            int32_t reset, hipStream_t s) {
-  hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(64), 0, s, st, gen, max_gen, target, reset);
+                            int32_t reset, hipStream_t s, unsigned long long* zero,
+                            int32_t n_zero) {
+  hipLaunchKernelGGL(set_state_kernel, dim3(1 + n_zero / 1024), dim3(64), 0, s, st, gen, max_gen,
+                     target, reset, zero, n_zero);
   return hipGetLastError();
 }
 
@@ -552,6 +534,261 @@ hipError_t launch_ga_next(const GAArgs& a, hipStream_t s) {
   const int n_slots = a.n_slots ? a.n_slots : a.P;
   const int n_waves = a.E + ((n_slots - a.E + 1) >> 1);
   hipLaunchKernelGGL(ga_next_kernel, dim3((n_waves + 3) / 4), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+
+// ------------------------------------------------- compact generation tail
+// Everything after the fitness launch of a small run's generation (CompactArgs;
+// compact_fits says which) in one launch: errors from the split partials, best
+// chromosome (and rank order, when the operators use it), stop test,
+// selection, crossover and mutation.  A generation of a small run is latency:
+// launches that reduce, rank and build took 3.8, 1.6 and 7.3 us for 50
+// chromosomes of 29 genes, most of the last in Philox blocks.  Here workgroups
+// of the fitness launch have made the draws and copied the population to a
+// fixed place (make_draw), so that every load of this launch is issued before
+// the first wait, and the rest happens in LDS: 4.9 us (7.9 with the loads
+// after one another).  With the fitness launch's own changes a generation went
+// from 22 to 10.7 us; that of 23 chromosomes of 9 genes from 19 to 10.
+//
+// Each workgroup computes all errors and selections for itself (a few KB to
+// read) and builds its share of the genes; workgroup 0 also writes errors,
+// order and state.  What decides (stop, generation) is what the fitness
+// launch recorded, so workgroup 0's update cannot be seen by another one.
+constexpr int kCompactThreads = 1024;
+constexpr int kCompactGenes = 4;     // genes per thread
+constexpr int kCompactPopulation = 512;
+constexpr int kCompactTotal = 16384; // genes in all: 64 KB of LDS, four workgroups
+constexpr int kCompactBlocks = 2;    // blocks of selection words per pair
+constexpr int kCompactDraws = (8 * kCompactBlocks - 2) / 2;  // largest tournament: 7
+
+__global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactArgs a) {
+  const RankArgs& ra = a.rank;
+  const GAArgs& g = a.ga;
+  RunState* st = ra.state;
+  const int P = g.P, K = g.K, E = g.E;
+  const int n_pairs = (P - E + 1) >> 1;
+  extern __shared__ uint64_t lds[];
+  uint64_t* keys = lds;                                       // [P]
+  double* e64 = reinterpret_cast<double*>(keys + P);          // [P]
+  double* cum = e64 + P;                                      // [P] (roulette)
+  uint64_t* words = reinterpret_cast<uint64_t*>(cum + P);     // [n_pairs * blocks * 4]
+  float* pop = reinterpret_cast<float*>(words + n_pairs * a.blocks * 4);   // [P * K]
+  int* order = reinterpret_cast<int*>(pop + P * K);           // [P]
+  int4* pair = reinterpret_cast<int4*>(lds + a.pair_at);      // [n_pairs] p1, p2, cross, cut
+  __shared__ int best_sh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kWaves = kCompactThreads / 64;
+
+  const int stop_seen = st->stop_seen, gen = st->gen_seen, max_gen = st->max_gen;
+  const double target = st->target;
+  const int n = P * K, first = blockIdx.x * kCompactThreads * kCompactGenes;
+  // Partials: groups of w = 2^x >= n_splits lanes take a chromosome each (lane
+  // l: split l).  Beyond 64 splits reduce_few_kernel has run.
+  const bool few = !a.reduced;
+  const int w = ra.n_splits <= 8 ? 8 : ra.n_splits <= 16 ? 16 : ra.n_splits <= 32 ? 32 : 64;
+  const int per = kCompactThreads / w;                        // chromosomes per round
+  const int sub = tid / w, l = tid & (w - 1);
+  constexpr int kRounds = 4;
+  double part[kRounds];
+  auto load_partials = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) {
+      const int i = i0 + u * per + sub;
+      const bool ok = i < P && l < ra.n_splits;
+      const double p = ra.partial[ok ? (int64_t)l * ra.ld_partial + i : 0];
+      part[u] = ok ? 0.0 + p : 0.0;
+    }
+  };
+  if (few) load_partials(0);
+  constexpr int kPop = 4;
+  float v[kPop];
+  auto load_pop = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < kPop; ++u) v[u] = a.cur[min(i0 + u * kCompactThreads, n - 1)];
+  };
+  load_pop(tid);
+  const int n_words = n_pairs * a.blocks * 4;
+  constexpr int kWords = kCompactPopulation / 2 * kCompactBlocks * 4 / kCompactThreads;
+  uint64_t word[kWords];
+#pragma unroll
+  for (int u = 0; u < kWords; ++u) word[u] = a.words[min(u * kCompactThreads + tid, n_words - 1)];
+  float mut[kCompactGenes];
+#pragma unroll
+  for (int u = 0; u < kCompactGenes; ++u)
+    mut[u] = a.mut[min(first + u * kCompactThreads + tid, n - 1)];
+  __builtin_amdgcn_sched_barrier(0);   // every load ahead of the first use
+  if (stop_seen) return;
+
+  // Errors: the sums of wave_split_sum (the lanes past the splits would only
+  // add zeros to the group's butterfly).
+  auto put_error = [&](int i, double e) {
+    const float f = (float)e;
+    e64[i] = e;
+    keys[i] = rank_key(f, i);
+    if (g.selection == 2) cum[i] = 1.0 / ((double)rank_key_value(f) + 1e-12);
+    if (blockIdx.x == 0 && few) {
+      ra.fit64[i] = e;
+      ra.fit32[i] = f;
+    }
+  };
+  if (few) {
+    for (int i0 = 0; i0 < P; i0 += per * kRounds) {
+      if (i0) load_partials(i0);
+#pragma unroll
+      for (int u = 0; u < kRounds; ++u) {
+        if (i0 + u * per >= P) break;
+        double s = part[u];
+        for (int o = w >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        const int i = i0 + u * per + sub;
+        if (l == 0 && i < P) put_error(i, error_from_sum(s, ra.NP, ra.error_fn));
+      }
+    }
+  } else {
+    for (int i = tid; i < P; i += kCompactThreads) put_error(i, ra.fit64[i]);
+  }
+  for (int i0 = tid; i0 < n; i0 += kPop * kCompactThreads) {
+    if (i0 != tid) load_pop(i0);
+#pragma unroll
+    for (int u = 0; u < kPop; ++u)
+      if (i0 + u * kCompactThreads < n) pop[i0 + u * kCompactThreads] = v[u];
+  }
+#pragma unroll
+  for (int u = 0; u < kWords; ++u)
+    if (u * kCompactThreads + tid < n_words) words[u * kCompactThreads + tid] = word[u];
+  __syncthreads();
+
+  // The last wave finds the best chromosome, tests the stop and updates the
+  // state while the others select.
+  if (wave == kWaves - 1) {
+    uint64_t best = ~0ull;
+    for (int i = lane; i < P; i += 64) best = min(best, keys[i]);
+    for (int o = 32; o > 0; o >>= 1)
+      best = min(best, (uint64_t)__shfl_xor((unsigned long long)best, o));
+    const int b = (int)(uint32_t)best;
+    const double err = e64[b];
+    const bool stop = err <= target || gen >= max_gen;
+    if (lane == 0) {
+      best_sh = stop ? -1 : b;
+      if (blockIdx.x == 0) {
+        st->best = b;
+        st->best_err = err;
+        st->evaluated = gen;
+        if (stop) st->stop = 1;
+        else st->gen = gen + 1;
+      }
+    }
+  }
+  if (a.need_order) {
+    for (int i = tid; i < P; i += kCompactThreads) {
+      const uint64_t ke = keys[i];
+      int r = 0;
+      for (int j = 0; j < P; ++j) r += keys[j] < ke ? 1 : 0;
+      order[r] = i;
+    }
+    __syncthreads();
+  }
+  if (g.selection == 2) {
+    if (tid == 0) {                        // left to right, as roulette_cum_body
+      double s = 0.0;
+      for (int i = 0; i < P; ++i) {
+        s += cum[i];
+        cum[i] = s;
+      }
+    }
+    __syncthreads();
+  }
+  if (tid < n_pairs) {
+    const int q = tid;
+    const uint32_t* wq = reinterpret_cast<const uint32_t*>(words + q * a.blocks * 4);
+    const int k = g.selection == 0 ? g.k : 1;
+    int4 c;
+    if (g.selection == 1) {
+      c.x = ranking_pick(order, P, wq[0]);
+      c.y = ranking_pick(order, P, wq[1]);
+    } else if (g.selection == 2) {
+      c.x = roulette_pick(cum, P, wq[0]);
+      c.y = roulette_pick(cum, P, wq[1]);
+    } else {
+      // Lowest (fitness, index) of each parent's draws: the smallest key, all
+      // keys read before the first comparison.
+      uint64_t key[2 * kCompactDraws];
+#pragma unroll
+      for (int d = 0; d < 2 * kCompactDraws; ++d)
+        key[d] = d < 2 * k ? keys[(int)(((uint64_t)wq[d] * (uint64_t)P) >> 32)] : ~0ull;
+      uint64_t b1 = ~0ull, b2 = ~0ull;
+#pragma unroll
+      for (int d = 0; d < 2 * kCompactDraws; ++d) {
+        if (d < k) b1 = min(b1, key[d]);
+        else b2 = min(b2, key[d]);
+      }
+      c.x = (int)(uint32_t)b1;
+      c.y = (int)(uint32_t)b2;
+    }
+    c.z = (uint64_t)wq[2 * k] < g.thr_cross ? 1 : 0;
+    c.w = 1 + (int)(((uint64_t)wq[2 * k + 1] * (uint64_t)(K - 1)) >> 32);
+    pair[q] = c;
+  }
+  __syncthreads();
+  const int best_i = best_sh;
+  if (best_i < 0) return;                  // stopped: no next generation
+  float* out = pick(((gen + 1) & 1) != 0, g.out_b, g.out_a);
+#pragma unroll
+  for (int u = 0; u < kCompactGenes; ++u) {
+    const int i = first + u * kCompactThreads + tid;
+    if (i >= n) break;
+    const int s = i / K, gi = i - s * K;
+    float x;
+    if (s < E) {
+      x = pop[(g.elite_mode == 0 ? best_i : order[s]) * K + gi];
+    } else {
+      const int4 c = pair[(s - E) >> 1];
+      const bool second = ((s - E) & 1) != 0;
+      const bool swapped = c.z && gi >= c.w;
+      x = pop[(second != swapped ? c.y : c.x) * K + gi];
+      if (!isnan(mut[u])) x = clamp_unit(__fadd_rn(x, mut[u]));
+    }
+    out[i] = x;
+    if (a.live) a.live[i] = x;
+  }
+}
+
+// LDS of the compact tail (bytes), and the offset of its pair table in words
+// of 8 bytes.
+static size_t compact_lds(int P, int K, int E, int blocks, int* pair_at) {
+  const size_t n_pairs = (size_t)(P - E + 1) / 2;
+  size_t b = (size_t)P * 24 + n_pairs * blocks * 32 + (size_t)P * K * 4 + (size_t)P * 4;
+  b = (b + 15) / 16 * 16;
+  if (pair_at) *pair_at = (int)(b / 8);
+  return b + n_pairs * sizeof(int4);
+}
+
+int compact_blocks(int k, int selection) { return (2 * (selection == 0 ? k : 1) + 2 + 7) / 8; }
+
+// Runs whose tail takes one launch; larger populations keep the separate
+// launches, which spread over more CUs.
+bool compact_fits(int P, int K, int k, int selection) {
+  return P <= kCompactPopulation && (int64_t)P * K <= kCompactTotal &&
+         compact_blocks(k, selection) <= kCompactBlocks;
+}
+
+hipError_t launch_compact_tail(CompactArgs a, hipStream_t s) {
+  const GAArgs& g = a.ga;
+  a.reduced = a.rank.n_splits > 64;
+  if (a.reduced) {
+    const hipError_t e = launch_reduce_few(a.rank, s);
+    if (e != hipSuccess) return e;
+  }
+  a.need_order = g.selection == 1 || (g.elite_mode == 1 && g.E > 0);
+  const size_t lds = compact_lds(g.P, g.K, g.E, a.blocks, &a.pair_at);
+  if (lds > 48 * 1024) {
+    const hipError_t e = hipFuncSetAttribute((const void*)compact_tail_kernel,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const int per = kCompactThreads * kCompactGenes;
+  hipLaunchKernelGGL(compact_tail_kernel, dim3((g.P * g.K + per - 1) / per), dim3(kCompactThreads),
+                     lds, s, a);
   return hipGetLastError();
 }
 

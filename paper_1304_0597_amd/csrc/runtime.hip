@@ -91,7 +91,7 @@ int check_config(const game_config* c, int32_t n_features) {
 }
 
 struct Layout {
-  size_t state, pop0, pop1, fit32, fit64, order, cum, partial, rescore, tally, cs, total;
+  size_t state, pop0, pop1, fit32, fit64, order, cum, partial, rescore, tally, words, mut, cs, total;
 };
 
 // The trig expansion's (cos x, sin x) table is kept for float32 runs (the
@@ -102,6 +102,12 @@ bool keeps_trig_table(const game_config* c) {
 
 // Classification sums; zeroed at create, and every launch leaves them zero.
 constexpr size_t kTallyBytes = kTallyChromosomes * 4 * sizeof(int64_t);
+
+// Float32 runs whose generation tail is one launch (compact_fits).
+bool compact_run(const game_config* c, int32_t K) {
+  return c->precision == GAME_FP32 &&
+         compact_fits(c->population, K, c->tournament_k, c->selection);
+}
 
 Layout layout(const game_config* c, int64_t n_patterns, int32_t n_features) {
   const size_t P = (size_t)c->population;
@@ -120,6 +126,13 @@ Layout layout(const game_config* c, int64_t n_patterns, int32_t n_features) {
   off += align_up(std::max(Ppad * kMaxSplits, (size_t)kSplitCapacity) * sizeof(double));
   L.rescore = off; off += align_up(64 * sizeof(double));
   L.tally = off; off += align_up(kTallyBytes);
+  L.words = off;
+  L.mut = off;
+  if (compact_run(c, (int32_t)K)) {
+    const size_t pairs = (P - c->elitism + 1) / 2;
+    off += align_up(pairs * compact_blocks(c->tournament_k, c->selection) * 4 * sizeof(uint64_t));
+    L.mut = off; off += 3 * align_up(P * K * sizeof(float));
+  }
   L.cs = off;
   if (keeps_trig_table(c)) off += align_up((size_t)n_patterns * n_features * 2 * sizeof(float));
   L.total = off;
@@ -147,6 +160,10 @@ struct game_ctx {
   double* cum;              // roulette wheel of the current generation
   double* partial;
   double* rescore;          // float64 error of the last re-scored elite
+  uint64_t* words;          // a compact generation's draws (DrawArgs)
+  float* mut;
+  float* cur;
+  float* live;              // the current population at a fixed place, during game_run
   unsigned long long* tally;// classification sums (kTallyBytes), zero between calls
   const float* cs;          // (cos x, sin x) of the data set (trig, float32), or null
   bool initialized;
@@ -488,14 +505,8 @@ int enqueue_screening(game_ctx* h, hipStream_t s) {
   return GAME_OK;
 }
 
-// The rest of a generation after its stop test: the roulette wheel when
-// selecting by roulette, then the genetic step (or, with a surrogate, the
-// screened generation tail) building pop[gen & 1] for the advanced counter.
-// Every kernel does nothing once the run has stopped.
-int enqueue_tail(game_ctx* h, hipStream_t s) {
-  if (h->cfg.selection == GAME_ROULETTE)
-    GAME_HIP(launch_roulette_cum(h->fit32, h->cfg.population, h->cum, &h->state->stop, s));
-  if (h->sur) return enqueue_screening(h, s);
+// Arguments of the genetic step of a run's generation.
+GAArgs step_args(const game_ctx* h) {
   GAArgs ga = ga_args(&h->cfg, h->K);
   ga.cum = h->cum;
   ga.pop_a = h->pop[0];
@@ -506,18 +517,55 @@ int enqueue_tail(game_ctx* h, hipStream_t s) {
   ga.order = h->order;
   ga.gen_ptr = &h->state->gen;
   ga.stop = &h->state->stop;
-  GAME_HIP(launch_ga_next(ga, s));
+  return ga;
+}
+
+// The rest of a generation after its stop test: the roulette wheel when
+// selecting by roulette, then the genetic step (or, with a surrogate, the
+// screened generation tail) building pop[gen & 1] for the advanced counter.
+// Every kernel does nothing once the run has stopped.
+int enqueue_tail(game_ctx* h, hipStream_t s) {
+  if (h->cfg.selection == GAME_ROULETTE)
+    GAME_HIP(launch_roulette_cum(h->fit32, h->cfg.population, h->cum, &h->state->stop, s));
+  if (h->sur) return enqueue_screening(h, s);
+  GAME_HIP(launch_ga_next(step_args(h), s));
   return GAME_OK;
 }
 
 // One generation of the loop on stream s: evaluate pop[gen & 1], finish and
 // rank, stop test, then build pop[(gen + 1) & 1].
-int enqueue_step(game_ctx* h, hipStream_t s) {
+// With `live` (a compact run's game_run) the population being evaluated is
+// h->live, and the tail writes the next one there too.
+int enqueue_step(game_ctx* h, hipStream_t s, bool live = false) {
   FitArgs fa = fit_args(h, h->X, h->t, h->NP, h->pop[0], h->cfg.population);
   fa.genes_alt = h->pop[1];
   fa.gen_sel = &h->state->gen;
   fa.stop = &h->state->stop;
   fa.stop_seen = &h->state->stop_seen;
+  // A small run's draws ride along with its fitness launch, and the rest of
+  // the generation is one launch.
+  const bool compact = !h->sur && compact_run(&h->cfg, h->K);
+  const GAArgs step = step_args(h);
+  if (compact) {
+    if (live) {
+      fa.genes = h->live;
+      fa.genes_alt = nullptr;
+    }
+    fa.gen_seen = &h->state->gen_seen;
+    DrawArgs& d = fa.draw;
+    d.seed = step.seed;
+    d.thr_mut = step.thr_mut;
+    d.sigma = step.sigma;
+    d.K = step.K;
+    d.E = step.E;
+    d.P = step.P;
+    d.n_pairs = (step.P - step.E + 1) / 2;
+    d.blocks = compact_blocks(step.k, step.selection);
+    d.words = h->words;
+    d.mut = h->mut;
+    d.cur = h->cur;
+    d.n_items = d.n_pairs * d.blocks + d.P * d.K;
+  }
   GAME_HIP(launch_fitness(h, fa, s));
   RankArgs ra{};
   ra.partial = h->partial;
@@ -530,6 +578,18 @@ int enqueue_step(game_ctx* h, hipStream_t s) {
   ra.fit64 = h->fit64;
   ra.order = h->order;
   ra.state = h->state;
+  if (compact) {
+    CompactArgs ca{};
+    ca.rank = ra;
+    ca.ga = step;
+    ca.words = h->words;
+    ca.mut = h->mut;
+    ca.cur = h->cur;
+    ca.live = live ? h->live : nullptr;
+    ca.blocks = fa.draw.blocks;
+    GAME_HIP(launch_compact_tail(ca, s));
+    return GAME_OK;
+  }
   GAME_HIP(launch_reduce_fitness(ra, s));
   GAME_HIP(launch_finish_rank(ra, s));
   return enqueue_tail(h, s);
@@ -541,6 +601,14 @@ __global__ void copy_current_kernel(const RunState* st, const float* pop0, const
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     out[i] = src[i];
+}
+
+hipError_t launch_copy_current(const RunState* st, const float* pop0, const float* pop1, int64_t n,
+                               float* out, hipStream_t s) {
+  const int64_t blocks = std::min<int64_t>((n + 255) / 256, 1024);
+  hipLaunchKernelGGL(copy_current_kernel, dim3((unsigned)blocks), dim3(256), 0, s, st, pop0, pop1,
+                     n, out);
+  return hipGetLastError();
 }
 
 // Queues up to n_chunks chunks of generations (enqueue() queues one) with
@@ -659,11 +727,12 @@ int game_create(const game_config* c, const float* X, const float* t, int64_t NP
   h->cum = (double*)(base + L.cum);
   h->rescore = (double*)(base + L.rescore);
   h->tally = (unsigned long long*)(base + L.tally);
-  hipError_t e = launch_fill_zero((float*)h->tally, kTallyBytes / sizeof(float), h->stream);
-  if (e != hipSuccess) {
-    delete h;
-    return hip_fail(e, "launch_fill_zero");
-  }
+  h->words = (uint64_t*)(base + L.words);
+  h->mut = (float*)(base + L.mut);
+  const size_t pop_bytes = align_up((size_t)c->population * h->K * sizeof(float));
+  h->cur = (float*)(base + L.mut + pop_bytes);
+  h->live = (float*)(base + L.mut + 2 * pop_bytes);
+  hipError_t e = hipSuccess;
   if (keeps_trig_table(c)) {
     float* cs = (float*)(base + L.cs);
     e = launch_trig_cs(X, NP, N, cs, h->stream);
@@ -680,7 +749,8 @@ int game_create(const game_config* c, const float* X, const float* t, int64_t NP
   }
   rc = create_chunk_sync(1, &h->host_state, h->chunk_done);
   if (rc == GAME_OK) {
-    e = launch_set_state(h->state, 0, c->max_generations, c->target, 1, h->stream);
+    e = launch_set_state(h->state, 0, c->max_generations, c->target, 1, h->stream, h->tally,
+                         kTallyBytes / sizeof(uint64_t));
     if (e != hipSuccess) rc = hip_fail(e, "launch_set_state");
   }
   if (rc) {
@@ -850,6 +920,8 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
   GAME_HIP(launch_set_state(h->state, 0, h->cfg.max_generations, h->cfg.target, resume ? 2 : 0,
                             h->stream));
   if (resume) {
+    // The rank order of the evaluation (a compact generation keeps none).
+    GAME_HIP(launch_rank(h->fit32, h->cfg.population, h->order, h->stream));
     const int rc = enqueue_tail(h, h->stream);
     if (rc) return rc;
     st.stop = 0;
@@ -873,6 +945,9 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
                                 });
     if (rc) return rc;
   } else if (!st.stop) {
+    const bool live = compact_run(&h->cfg, h->K);
+    if (live) GAME_HIP(launch_copy_current(h->state, h->pop[0], h->pop[1],
+                                           (int64_t)h->cfg.population * h->K, h->live, h->stream));
     if (!h->graph) {
       // Capture a fixed number of generations once; every kernel reads the
       // generation counter and the stop flag from device memory, so the
@@ -880,7 +955,7 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
       const int steps = 8;
       GAME_HIP(hipStreamBeginCapture(h->capture_stream, hipStreamCaptureModeThreadLocal));
       int rc = GAME_OK;
-      for (int i = 0; i < steps && rc == GAME_OK; ++i) rc = enqueue_step(h, h->capture_stream);
+      for (int i = 0; i < steps && rc == GAME_OK; ++i) rc = enqueue_step(h, h->capture_stream, live);
       hipGraph_t g = nullptr;
       const hipError_t ec = hipStreamEndCapture(h->capture_stream, &g);
       if (rc) {
@@ -933,10 +1008,8 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
 int game_get_population(game_t h, float* genes, float* fitness) {
   if (!h) return fail(GAME_EINVAL, "handle is NULL");
   if (!genes) return fail(GAME_EINVAL, "genes is NULL");
-  const int64_t n = (int64_t)h->cfg.population * h->K;
-  hipLaunchKernelGGL(copy_current_kernel, dim3((unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024)),
-                     dim3(256), 0, h->stream, h->state, h->pop[0], h->pop[1], n, genes);
-  GAME_HIP(hipGetLastError());
+  GAME_HIP(launch_copy_current(h->state, h->pop[0], h->pop[1],
+                               (int64_t)h->cfg.population * h->K, genes, h->stream));
   if (fitness)
     GAME_HIP(hipMemcpyAsync(fitness, h->fit32, sizeof(float) * h->cfg.population,
                             hipMemcpyDeviceToDevice, h->stream));
@@ -1872,11 +1945,8 @@ int game_batch_get_population(game_batch_t b, int32_t run, float* genes, float* 
   if (run < 0 || run >= b->n_runs) return fail(GAME_EINVAL, "run %d out of range", run);
   if (!genes) return fail(GAME_EINVAL, "genes is NULL");
   const BatchRun& r = b->runs[run];
-  const int64_t n = (int64_t)r.P * r.K;
-  hipLaunchKernelGGL(copy_current_kernel,
-                     dim3((unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024)), dim3(256),
-                     0, b->stream, b->states + run, r.pop0, r.pop1, n, genes);
-  GAME_HIP(hipGetLastError());
+  GAME_HIP(launch_copy_current(b->states + run, r.pop0, r.pop1, (int64_t)r.P * r.K, genes,
+                               b->stream));
   if (fitness)
     GAME_HIP(hipMemcpyAsync(fitness, r.fit32, sizeof(float) * r.P, hipMemcpyDeviceToDevice,
                             b->stream));

@@ -324,3 +324,40 @@ def test_step_errors_are_the_fitness_launch_bits(gg, shape, error_fn):
         ref = g.fitness(pop)
         assert np.array_equal(bits(fit.cpu().numpy()), bits(ref.cpu().numpy()))
     g.close()
+
+
+@pytest.mark.parametrize("case", [
+    # (NP, N, d, P): smallest, odd population, the limits of the one-launch
+    # tail (16,384 genes, 512 chromosomes, tournaments of 7) and one past each,
+    # more than 64 pattern splits
+    (1, 1, 1, 2, {}), (300, 5, 2, 23, dict(tournament_k=7)),
+    (300, 5, 2, 23, dict(tournament_k=8)), (700, 31, 1, 512, dict(elitism=0)),
+    (700, 31, 1, 511, dict(elite_mode=1, elitism=5)), (500, 63, 2, 129, dict(selection=1)),
+    (500, 64, 2, 129, dict(selection=1)), (900, 3, 2, 513, dict(selection=2)),
+    (20001, 8, 1, 23, dict(selection=2, elitism=1, elite_mode=1)),
+    (20001, 8, 1, 23, dict(error_fn=2, p_mutation=1.0))],
+    ids=lambda c: f"{c[0]}x{c[1]}-d{c[2]}-P{c[3]}-" + "-".join(f"{k}{v}" for k, v in c[4].items()))
+def test_generation_tail_at_its_edges(gg, case):
+    """Every generation equals the oracle's built from the device's errors,
+    stepped and in a captured run; those errors are game_fitness's bits."""
+    NP, N, d, P, kw = case
+    rng = np.random.default_rng(NP + P)
+    X = torch.from_numpy(rng.uniform(-1, 1, (NP, N)).astype(np.float32)).cuda()
+    t = torch.from_numpy((rng.random(NP) < 0.5).astype(np.float32)).cuda()
+    kw = dict(dict(tournament_k=min(3, P), elitism=min(2, P - 1)), **kw)
+    c = gg.config(basis=0, degree=d, population=P, seed=7, max_generations=3, target=-1.0, **kw)
+    g = gg.Game(c, X, t)
+    g.init_population()
+    for gen in range(3):
+        pop, _ = g.population()
+        ref = g.fitness(pop)
+        g.step()
+        nxt, fit = g.population()
+        pop, ref, nxt, fit = (x.cpu().numpy() for x in (pop, ref, nxt, fit))
+        assert np.array_equal(bits(fit), bits(ref)), gen
+        assert np.array_equal(bits(nxt), bits(oga.ga_next(pop, fit, gen + 1, oracle_cfg(c)))), gen
+    g.init_population()
+    gens, _, _ = g.run()
+    assert gens == 3
+    assert np.array_equal(bits(g.population()[0].cpu().numpy()), bits(nxt))
+    g.close()
