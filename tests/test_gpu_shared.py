@@ -124,3 +124,25 @@ def test_paper_shaped_run_follows_oracle(gg):
     assert abs(err - ref[0]) <= 1e-5 * ref[0] + 1e-7 * float(np.mean(t.astype(np.float64) ** 2)) \
         + budget[0], (err, ref[0], budget[0])
     g.close()
+
+
+@pytest.mark.parametrize("d", [1, 5, 16])
+@pytest.mark.parametrize("NP,N", [(1, 16), (257, 17), (70000, 17), (65536, 33), (300, 64)])
+def test_trig_sums_over_all_angles(gg, d, NP, N):
+    """Every quadrant, angles at and next to multiples of pi/2, both sides of
+    the largest angle reduced in the kernel (65,536) and far beyond it, rows
+    read directly and staged; infinities and NaN give NaN in their row only."""
+    rng = np.random.default_rng(NP + N + d)
+    X = (rng.uniform(-1, 1, (NP, N)) * 10.0 ** rng.integers(-6, 8, (NP, N))).astype(np.float32)
+    flat = X.reshape(-1)
+    k = np.arange(min(flat.size, 64))
+    edge = (k * (np.pi / 2)).astype(np.float32)
+    flat[:k.size] = np.where(k % 3 == 0, edge, np.nextafter(edge, np.float32(9e9) * (-1) ** k))
+    flat[-4:] = np.float32([65536.0, -65536.0, np.nextafter(np.float32(65536), np.float32(9e9)), 0])
+    Z = gg.game_trig_sums(torch.from_numpy(X).cuda(), d).cpu().numpy().astype(np.float64)
+    ref = og.shared_trig_sums(X, d)
+    assert np.all(np.abs(Z - ref) <= 2.0 ** -24 * np.abs(ref) + N * d * 1e-15)
+    if NP > 2:
+        X[0, 0], X[1, N - 1] = np.inf, np.nan
+        Z2 = gg.game_trig_sums(torch.from_numpy(X).cuda(), d).cpu().numpy().astype(np.float64)
+        assert np.isnan(Z2[:2]).all() and np.array_equal(Z2[2:], Z[2:])
