@@ -411,17 +411,21 @@ __device__ __forceinline__ float sum_ranges(const float* part, int ks, int64_t n
 // Adam (Kingma & Ba) with bias correction, parameter i, at Adam step `step`
 // (1 for the first update).  The moment updates are explicit FMAs, so the
 // result does not depend on the translation unit's contraction setting.
+// Nothing changes when skipped is set (tested once the loads are issued).
 __device__ __forceinline__ void adam_update(float* p, const float* part, int ks, float* m, float* v,
-                                            int64_t n, float lr, int step, int64_t i) {
+                                            int64_t n, float lr, int step, int64_t i,
+                                            int32_t skipped) {
+  const float m0 = m[i], v0 = v[i], p0 = p[i];
+  const float gi = sum_ranges(part, ks, n, i);
   const float c1 = 1.f - powf(0.9f, (float)step);
   const float c2 = 1.f - powf(0.999f, (float)step);
   const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
-  const float gi = sum_ranges(part, ks, n, i);
-  const float mi = fmaf(beta1, m[i], (1.f - beta1) * gi);
-  const float vi = fmaf(beta2, v[i], ((1.f - beta2) * gi) * gi);
+  if (skipped) return;
+  const float mi = fmaf(beta1, m0, (1.f - beta1) * gi);
+  const float vi = fmaf(beta2, v0, ((1.f - beta2) * gi) * gi);
   m[i] = mi;
   v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  p[i] = p0 - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 // Adam on n parameters whose gradient is the sum of ks ranges

@@ -1057,25 +1057,39 @@ __global__ __launch_bounds__(1024) void gene_moments_kernel(const float* genes, 
   }
 }
 
-__global__ void gene_stats_kernel(const double* part, int K, const SurrogateState* st,
-                                  const RunState* run, float* mu, float* inv) {
+// Workgroup b: genes [8 b, 8 b + 8).  All shares of its genes are loaded at
+// once; one thread per gene adds them in workgroup order from LDS.
+constexpr int kStatGenes = 8;
+__global__ __launch_bounds__(kMomentBlocks) void gene_stats_kernel(
+    const double* part, int K, const SurrogateState* st, const RunState* run, float* mu,
+    float* inv) {
+  __shared__ double sh[2][kMomentBlocks][kStatGenes + 1];
   if (run->stop) return;
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
   const int count = st->count;
-  if (g >= K || count < 1) return;
+  const int g0 = blockIdx.x * kStatGenes;
+  double v[2][kStatGenes];
+#pragma unroll
+  for (int u = 0; u < kStatGenes; ++u) {
+    // consecutive threads read consecutive genes of a share
+    const int e = threadIdx.x + u * kMomentBlocks, k = e / kStatGenes, g = e % kStatGenes;
+    const int64_t at = (int64_t)k * K + min(g0 + g, K - 1);
+    v[0][u] = part[at];
+    v[1][u] = part[(int64_t)kMomentBlocks * K + at];
+  }
+#pragma unroll
+  for (int u = 0; u < kStatGenes; ++u) {
+    const int e = threadIdx.x + u * kMomentBlocks, k = e / kStatGenes, g = e % kStatGenes;
+    sh[0][k][g] = v[0][u];
+    sh[1][k][g] = v[1][u];
+  }
+  __syncthreads();
+  const int t = threadIdx.x, g = g0 + t;
+  if (t >= kStatGenes || g >= K || count < 1) return;
   double a = 0.0, b = 0.0;
-  for (int k0 = 0; k0 < kMomentBlocks; k0 += kMomentRows) {
-    double pa[kMomentRows], pb[kMomentRows];
-#pragma unroll
-    for (int u = 0; u < kMomentRows; ++u) {
-      pa[u] = part[(int64_t)(k0 + u) * K + g];
-      pb[u] = part[(int64_t)(kMomentBlocks + k0 + u) * K + g];
-    }
-#pragma unroll
-    for (int u = 0; u < kMomentRows; ++u) {
-      a += pa[u];
-      b += pb[u];
-    }
+#pragma unroll 8
+  for (int k = 0; k < kMomentBlocks; ++k) {
+    a += sh[0][k][t];
+    b += sh[1][k][t];
   }
   const double m = a / count;
   const double var = fmax(b / count - m * m, 0.0);
@@ -1091,8 +1105,8 @@ hipError_t launch_gene_stats(const float* genes, int32_t K, int32_t capacity,
                      capacity, st, run, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(gene_stats_kernel, dim3((K + 255) / 256), dim3(256), 0, s, part, K, st, run,
-                     mu, inv);
+  hipLaunchKernelGGL(gene_stats_kernel, dim3((K + kStatGenes - 1) / kStatGenes),
+                     dim3(kMomentBlocks), 0, s, part, K, st, run, mu, inv);
   return hipGetLastError();
 }
 
@@ -1124,27 +1138,41 @@ hipError_t launch_standardize(const float* src, int32_t n, int32_t K, const floa
 // Minibatch of B archive rows drawn with replacement: row b is
 // (u32 * count) >> 32 with u32 = lo32(o0) of key (seed, 3), counter
 // (generation, 1 + step, b, 0); genes and targets standardised.
-__device__ __forceinline__ void sample_minibatch_body(int64_t i, const float* genes,
+// One wave per row b: its lanes share the draw and stride over the genes.
+__device__ __forceinline__ void sample_minibatch_body(int b, const float* genes,
                                                       const float* target, int K,
                                                       const SurrogateState* st,
                                                       const RunState* run, uint64_t seed, int step,
                                                       int B, const float* mu, const float* inv,
                                                       float* Xb, float* tb) {
-  if (i >= (int64_t)B * K) return;
-  const int b = (int)(i / K), g = (int)(i - (int64_t)b * K);
+  if (b >= B) return;
+  const int lane = threadIdx.x & 63;
   const U64x4 r = draw(seed, 3, (uint64_t)run->evaluated, (uint64_t)(1 + step), (uint64_t)b);
   const int idx = (int)(((r.o0 & 0xFFFFFFFFull) * (uint64_t)st->count) >> 32);
-  Xb[i] = standardize1(genes[(int64_t)idx * K + g], mu[g], inv[g]);
-  if (g == 0) tb[b] = (target[idx] - st->mean) * st->inv_std;
+  const float* src = genes + (int64_t)idx * K;
+  constexpr int kU = 4;
+  for (int g0 = lane; g0 < K; g0 += 64 * kU) {
+    float v[kU], m[kU], s[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int g = min(g0 + 64 * u, K - 1);
+      v[u] = src[g];
+      m[u] = mu[g];
+      s[u] = inv[g];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (g0 + 64 * u < K) Xb[(int64_t)b * K + g0 + 64 * u] = standardize1(v[u], m[u], s[u]);
+  }
+  if (lane == 0) tb[b] = (target[idx] - st->mean) * st->inv_std;
 }
 
-__global__ void sample_minibatch_kernel(const float* genes, const float* target, int K,
-                                        const SurrogateState* st, const RunState* run,
-                                        uint64_t seed, int step, int B, const float* mu,
-                                        const float* inv, float* Xb, float* tb) {
+__global__ __launch_bounds__(256) void sample_minibatch_kernel(
+    const float* genes, const float* target, int K, const SurrogateState* st, const RunState* run,
+    uint64_t seed, int step, int B, const float* mu, const float* inv, float* Xb, float* tb) {
   if (run->stop) return;
-  sample_minibatch_body((int64_t)blockIdx.x * blockDim.x + threadIdx.x, genes, target, K, st, run,
-                        seed, step, B, mu, inv, Xb, tb);
+  sample_minibatch_body(blockIdx.x * 4 + (int)(threadIdx.x >> 6), genes, target, K, st, run, seed,
+                        step, B, mu, inv, Xb, tb);
 }
 
 // Workgroups [0, adam_blocks) update the parameters; the rest draw the next
@@ -1154,14 +1182,15 @@ __global__ void adam_sample_kernel(float* p, const float* part, int ks, float* m
                                    int adam_blocks, const float* genes, const float* target, int K,
                                    const RunState* run, uint64_t seed, int next_step, int B,
                                    const float* mu, const float* inv, float* Xb, float* tb) {
-  if (skip && *skip) return;
+  const int32_t skipped = skip ? *skip : 0;
   if ((int)blockIdx.x < adam_blocks) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) adam_update(p, part, ks, m, v, n, lr, st->step, i);
+    if (i < n) adam_update(p, part, ks, m, v, n, lr, st->step, i, skipped);
     return;
   }
-  sample_minibatch_body((int64_t)(blockIdx.x - adam_blocks) * blockDim.x + threadIdx.x, genes,
-                        target, K, st, run, seed, next_step, B, mu, inv, Xb, tb);
+  if (skipped) return;
+  sample_minibatch_body(((int)blockIdx.x - adam_blocks) * 4 + (int)(threadIdx.x >> 6), genes, target,
+                        K, st, run, seed, next_step, B, mu, inv, Xb, tb);
 }
 
 hipError_t launch_adam_sample(float* p, const float* part, int ks, float* m, float* v, int64_t n,
@@ -1170,7 +1199,7 @@ hipError_t launch_adam_sample(float* p, const float* part, int ks, float* m, flo
                               int32_t next_step, int32_t B, const float* mu, const float* inv,
                               float* Xb, float* tb, hipStream_t s) {
   const int adam_blocks = (int)((n + 255) / 256);
-  const int sample_blocks = (int)(((int64_t)B * K + 255) / 256);
+  const int sample_blocks = (B + 3) / 4;
   hipLaunchKernelGGL(adam_sample_kernel, dim3((unsigned)(adam_blocks + sample_blocks)), dim3(256),
                      0, s, p, part, ks, m, v, n, lr, st, skip, adam_blocks, genes, target, K, run,
                      seed, next_step, B, mu, inv, Xb, tb);
@@ -1181,9 +1210,7 @@ hipError_t launch_sample_minibatch(const float* genes, const float* target, int3
                                    const SurrogateState* st, const RunState* run, uint64_t seed,
                                    int32_t step, int32_t B, const float* mu, const float* inv,
                                    float* Xb, float* tb, hipStream_t s) {
-  const int64_t n = (int64_t)B * K;
-  hipLaunchKernelGGL(sample_minibatch_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                     genes, target, K, st, run, seed, step, B, mu, inv, Xb, tb);
+  hipLaunchKernelGGL(sample_minibatch_kernel, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, s, genes, target, K, st, run, seed, step, B, mu, inv, Xb, tb);
   return hipGetLastError();
 }
 
@@ -1227,14 +1254,41 @@ __global__ __launch_bounds__(1024) void spearman_gate_kernel(const float* pred, 
     if (threadIdx.x == 0) st->skip = 1;
     return;
   }
+  // Ranks by counting, 1024 / A2 threads per item (A2: A rounded up to a power
+  // of two), the values in LDS.
   const int i = threadIdx.x;
+  float* vp = reinterpret_cast<float*>(saa);
+  float* ve = reinterpret_cast<float*>(sbb);
+  int* cnt = reinterpret_cast<int*>(sab);
   if (i < A) {
-    const float p = rank_key_value(pred[i]), e = rank_key_value(exact[i]);
+    vp[i] = rank_key_value(pred[i]);
+    ve[i] = rank_key_value(exact[i]);
+  }
+  int a2 = 64;
+  while (a2 < A) a2 <<= 1;
+  const int parts = 1024 / a2, item = i & (a2 - 1), part = i / a2;
+  cnt[2 * i] = cnt[2 * i + 1] = 0;
+  __syncthreads();
+  if (item < A) {
+    const float p = vp[item], e = ve[item];
     int cp = 0, ce = 0;
-    for (int j = 0; j < A; ++j) {
-      const float pj = rank_key_value(pred[j]), ej = rank_key_value(exact[j]);
-      cp += (pj < p || (pj == p && j < i)) ? 1 : 0;
-      ce += (ej < e || (ej == e && j < i)) ? 1 : 0;
+    const int per = (A + parts - 1) / parts;
+    const int j1 = min((part + 1) * per, A);
+#pragma unroll 4
+    for (int j = part * per; j < j1; ++j) {
+      const float pj = vp[j], ej = ve[j];
+      cp += (pj < p || (pj == p && j < item)) ? 1 : 0;
+      ce += (ej < e || (ej == e && j < item)) ? 1 : 0;
+    }
+    cnt[2 * i] = cp;
+    cnt[2 * i + 1] = ce;
+  }
+  __syncthreads();
+  if (i < A) {
+    int cp = 0, ce = 0;
+    for (int k = 0; k < parts; ++k) {
+      cp += cnt[2 * (k * a2 + i)];
+      ce += cnt[2 * (k * a2 + i) + 1];
     }
     ra[i] = (float)cp;
     rb[i] = (float)ce;

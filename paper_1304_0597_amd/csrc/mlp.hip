@@ -24,6 +24,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -108,7 +109,6 @@ __device__ __forceinline__ void stage_slice(float* S, const float* X, int64_t ld
 // depend on how many rows the product has (the network's predictions for a
 // chromosome are the same in any batch).
 constexpr int kSmallWaves = 8;
-constexpr int kSmallSteps = 4;
 constexpr int kSmallMaxM = 4096;
 
 // Epilogue of output (m, n) with the product value z.
@@ -188,13 +188,18 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g) {
 // of each operand X.  When the row index is the unit stride (or the operand
 // has one row) each lane loads its own values: a load instruction reads
 // consecutive addresses.  When k is the unit stride, the wave instead loads
-// its 32 rows x 64 k block along k (one row per instruction), writes it to
-// its own LDS area and reads its values back.  A wave loads up to
-// kSmallSteps steps per round, every load of the round issued before the
-// first wait.  The waves' partial tiles (and row sums) are added in wave
+// its 32 rows x 16 T k block along k, writes it to its own LDS area and reads
+// its values back.  A wave loads T steps per round (2 when its whole range is
+// no longer: 256 values of K, else 4), every load of the round issued before
+// the first wait.  The waves' partial tiles (and row sums) are added in wave
 // order through LDS (over the staging areas, after a barrier).
-constexpr int kStageLd = 68;                    // staged row: 64 k values + 4 (16-byte rows)
-constexpr int kStageFloats = 32 * kStageLd;     // one operand of one wave
+//
+// A launch is a chain of latencies: arguments, loads, the turn through LDS,
+// MFMAs, the sum over waves.  1,024 x 256 x 256 (forward layer): 6.0 us, 8.8 with
+// rounds of 4 steps, a clamped address per load and the skip flag read first.
+constexpr int stage_ld(int t) { return 16 * t + 4; }    // staged row: 16 t values, 16-byte rows
+constexpr int stage_floats(int t) { return 32 * stage_ld(t); }   // one operand of one wave
+__host__ __device__ inline int round_steps(int steps_per_wave) { return steps_per_wave <= 2 ? 2 : 4; }
 
 template <bool STAGED>
 struct SmallOperand {
@@ -208,23 +213,38 @@ __host__ __device__ inline bool small_staged(int64_t ld_r, int64_t ld_k, int R) 
   return ld_k == 1 && ld_r != 1 && R > 1;
 }
 
-// Issues the loads of a round (steps s0 ..) into raw[32], branch-free so
-// that both operands' loads are in flight together: load j reads row
-// row0 + j at k = 16 s0 + lane (staged), or row row0 + r at
-// k = 16 (s0 + j / 8) + 8 h + j % 8 (direct); clamped into the operand.
-// Offsets are 32-bit byte offsets from the operand's base (the launch
-// checks that every operand spans less than 4 GiB), so each load needs one
-// address register.
-template <bool STAGED>
+// Issues the loads of a round (steps s0 ..) into raw[8 T], branch-free so
+// that both operands' loads are in flight together.  Staged: load j reads
+// rows row0 + j (4 / T) + lane / (16 T) at k = 16 s0 + lane % (16 T).  Direct:
+// load j reads row row0 + r at k = 16 (s0 + j / 8) + 8 h + j % 8.  Inside the
+// operand the part of the address that changes from load to load is uniform
+// (scalar); at its edges rows and k are clamped into it.  Offsets are 32-bit
+// byte offsets from the operand's base (the launch checks that every operand
+// spans less than 4 GiB).
+template <bool STAGED, int T>
 __device__ __forceinline__ void small_issue(const SmallOperand<STAGED>& o, int s0, int K, int lane,
-                                            float (&raw)[32]) {
+                                            float (&raw)[8 * T]) {
   const int r = lane & 31, h = lane >> 5;
   const uint32_t ldr = (uint32_t)o.ld_r * 4u, ldk = (uint32_t)o.ld_k * 4u;
   const char* base = reinterpret_cast<const char*>(o.X);
+  constexpr int RPI = 4 / T;                    // rows per staged load
+  const int kk = s0 * 16 + (lane & (16 * T - 1)), rsub = lane / (16 * T);
+  const bool inside = STAGED ? o.row0 + 32 <= o.R : (s0 + T) * 16 <= K;
+  if (inside) {
+    const uint32_t lane_off = STAGED ? rsub * ldr + (uint32_t)min(kk, K - 1) * ldk
+                                     : (uint32_t)min(o.row0 + r, o.R - 1) * ldr + 8u * h * ldk;
 #pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    const int row = o.row0 + (STAGED ? j : r);
-    const int k = STAGED ? s0 * 16 + lane : (s0 + (j >> 3)) * 16 + 8 * h + (j & 7);
+    for (int j = 0; j < 8 * T; ++j) {
+      const uint32_t u = STAGED ? (uint32_t)(o.row0 + j * RPI) * ldr
+                                : (uint32_t)((s0 + (j >> 3)) * 16 + (j & 7)) * ldk;
+      raw[j] = *reinterpret_cast<const float*>(base + u + lane_off);
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < 8 * T; ++j) {
+    const int row = o.row0 + (STAGED ? j * RPI + rsub : r);
+    const int k = STAGED ? kk : (s0 + (j >> 3)) * 16 + 8 * h + (j & 7);
     const uint32_t off = (uint32_t)min(row, o.R - 1) * ldr + (uint32_t)min(k, K - 1) * ldk;
     raw[j] = *reinterpret_cast<const float*>(base + off);
   }
@@ -232,24 +252,26 @@ __device__ __forceinline__ void small_issue(const SmallOperand<STAGED>& o, int s
 
 // The round's values of lane (r, h), zero outside rows < R, k < K and
 // steps < se.
-template <bool STAGED>
+template <bool STAGED, int T>
 __device__ __forceinline__ void small_finish(const SmallOperand<STAGED>& o, int s0, int se, int K,
-                                             int lane, const float (&raw)[32],
-                                             float (&val)[kSmallSteps][8]) {
+                                             int lane, const float (&raw)[8 * T],
+                                             float (&val)[T][8]) {
   const int r = lane & 31, h = lane >> 5;
   if constexpr (STAGED) {
-    const int k = s0 * 16 + lane;
+    constexpr int RPI = 4 / T, LD = stage_ld(T);
+    const int kc = lane & (16 * T - 1), k = s0 * 16 + kc, rsub = lane / (16 * T);
     const bool kok = k < K && (k >> 4) < se;
 #pragma unroll
-    for (int j = 0; j < 32; ++j) o.stage[j * kStageLd + lane] = keep_if(raw[j], kok && o.row0 + j < o.R);
+    for (int j = 0; j < 8 * T; ++j)
+      o.stage[(j * RPI + rsub) * LD + kc] = keep_if(raw[j], kok && o.row0 + j * RPI + rsub < o.R);
 #pragma unroll
-    for (int i = 0; i < kSmallSteps; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-      for (int v = 0; v < 8; ++v) val[i][v] = o.stage[r * kStageLd + i * 16 + 8 * h + v];
+      for (int v = 0; v < 8; ++v) val[i][v] = o.stage[r * LD + i * 16 + 8 * h + v];
   } else {
     const bool rok = o.row0 + r < o.R;
 #pragma unroll
-    for (int i = 0; i < kSmallSteps; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
       for (int v = 0; v < 8; ++v) {
         const int k = (s0 + i) * 16 + 8 * h + v;
@@ -258,54 +280,65 @@ __device__ __forceinline__ void small_finish(const SmallOperand<STAGED>& o, int 
   }
 }
 
+// Steps of the longest range of one wave.
+__host__ __device__ inline int small_steps_per_wave(int K, int k_split) {
+  const int steps = (K + 15) >> 4;
+  const int per_z = (steps + k_split - 1) / k_split;
+  return (per_z + kSmallWaves - 1) / kSmallWaves;
+}
+
 size_t small_lds_bytes(const GemmArgs& g) {
   const int st = (small_staged(g.lda_m, g.lda_k, g.M) ? 1 : 0) +
                  (small_staged(g.ldb_n, g.ldb_k, g.N) ? 1 : 0);
-  const size_t stage = (size_t)kSmallWaves * st * kStageFloats;
+  const int t = round_steps(small_steps_per_wave(g.K, g.k_split));
+  const size_t stage = (size_t)kSmallWaves * st * stage_floats(t);
   const size_t red = (size_t)kSmallWaves * 32 * 32;
   return ((size_t)kSmallWaves * 64 + (stage > red ? stage : red)) * sizeof(float);
 }
 
-// One launch may carry up to kMaxProducts independent products (row tiles
-// [ty_end[p-1], ty_end[p]) serve product p); each product's workgroups take
-// the operand-layout variant of its own operands.
+// One launch may carry up to kMaxProducts independent products (workgroups
+// [end[p-1], end[p]) serve product p, column tiles fastest, then row tiles,
+// then K ranges); each product's workgroups take the operand-layout variant of
+// its own operands.
 constexpr int kMaxProducts = 3;
+template <int NP>
 struct GemmMulti {
-  GemmArgs g[kMaxProducts];
-  int32_t ty_end[kMaxProducts];
-  int32_t n;
+  GemmArgs g[NP];
+  int32_t end[NP];
 };
 
-template <bool BF16, bool SA, bool SB>
-__device__ __forceinline__ void small_body(const GemmArgs& g, int by, float* small_lds) {
+template <bool BF16, bool SA, bool SB, int T>
+__device__ __forceinline__ void small_body(const GemmArgs& g, int bx, int by, int bz,
+                                           float* small_lds) {
   float* red_rs = small_lds;                            // [waves][64]
   float* red = small_lds + kSmallWaves * 64;            // [waves][32 * 32], over the staging areas
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int r = lane & 31, h = lane >> 5;
-  const int m0 = by * 32, n0 = blockIdx.x * 32;
+  const int m0 = by * 32, n0 = bx * 32;
   const int steps = (g.K + 15) >> 4;
   const int per_z = (steps + g.k_split - 1) / g.k_split;
-  const int zb = min(steps, (int)blockIdx.z * per_z), ze = min(steps, zb + per_z);
+  const int zb = min(steps, bz * per_z), ze = min(steps, zb + per_z);
   const int per_w = (ze - zb + kSmallWaves - 1) / kSmallWaves;
   const int wb = min(ze, zb + wave * per_w), we = min(ze, wb + per_w);
-  float* area = red + wave * ((SA ? 1 : 0) + (SB ? 1 : 0)) * kStageFloats;
+  float* area = red + wave * ((SA ? 1 : 0) + (SB ? 1 : 0)) * stage_floats(T);
   const SmallOperand<SA> oa{g.A, g.lda_m, g.lda_k, m0, g.M, area};
-  const SmallOperand<SB> ob{g.B, g.ldb_n, g.ldb_k, n0, g.N, area + (SA ? kStageFloats : 0)};
+  const SmallOperand<SB> ob{g.B, g.ldb_n, g.ldb_k, n0, g.N, area + (SA ? stage_floats(T) : 0)};
   f32x16 acc = f32x16{};
   float rs = 0.f;
-  for (int s0 = wb; s0 < we; s0 += kSmallSteps) {
-    float ra[32], rb[32];
-    small_issue(oa, s0, g.K, lane, ra);
-    small_issue(ob, s0, g.K, lane, rb);
+  const int32_t skipped = g.skip ? *g.skip : 0;
+  for (int s0 = wb; s0 < we; s0 += T) {
+    float ra[8 * T], rb[8 * T];
+    small_issue<SA, T>(oa, s0, g.K, lane, ra);
+    small_issue<SB, T>(ob, s0, g.K, lane, rb);
     __builtin_amdgcn_sched_barrier(0);   // keep every load ahead of the first use
-    float av[kSmallSteps][8], bv[kSmallSteps][8];
-    small_finish(oa, s0, we, g.K, lane, ra, av);
-    small_finish(ob, s0, we, g.K, lane, rb, bv);
+    float av[T][8], bv[T][8];
+    small_finish<SA, T>(oa, s0, we, g.K, lane, ra, av);
+    small_finish<SB, T>(ob, s0, we, g.K, lane, rb, bv);
     // Steps past the wave's range hold zeros: running their MFMAs keeps the
     // code free of branches.
 #pragma unroll
-    for (int i = 0; i < kSmallSteps; ++i) {
+    for (int i = 0; i < T; ++i) {
 #pragma unroll
       for (int v = 0; v < 8; ++v) rs += av[i][v];
       if constexpr (BF16) {
@@ -323,6 +356,7 @@ __device__ __forceinline__ void small_body(const GemmArgs& g, int by, float* sma
       }
     }
   }
+  if (skipped) return;   // tested here, under the loads
   __syncthreads();   // every wave is done with its staging area
   // Accumulator register i of lane (r, h) is C row 8 (i / 4) + 4 h + i % 4,
   // column r.
@@ -338,38 +372,44 @@ __device__ __forceinline__ void small_body(const GemmArgs& g, int by, float* sma
     float z = red[o];
 #pragma unroll
     for (int w = 1; w < kSmallWaves; ++w) z += red[w * 32 * 32 + o];
-    if (split) g.part[(int64_t)blockIdx.z * g.part_ld + (int64_t)mm * g.ldc + nn] = z;
+    if (split) g.part[(int64_t)bz * g.part_ld + (int64_t)mm * g.ldc + nn] = z;
     else gemm_store(g, mm, nn, z);
   }
   // Row sums of A over the range (the first column tile computes them):
   // the two lane halves of each wave, waves in order.
-  if (g.rowsum_part && blockIdx.x == 0 && threadIdx.x < 32 && m0 + (int)threadIdx.x < g.M) {
+  if (g.rowsum_part && bx == 0 && threadIdx.x < 32 && m0 + (int)threadIdx.x < g.M) {
     const int t = threadIdx.x;
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < kSmallWaves; ++w) v += red_rs[w * 64 + t] + red_rs[w * 64 + t + 32];
-    g.rowsum_part[(int64_t)blockIdx.z * g.part_ld + m0 + t] = v;
+    g.rowsum_part[(int64_t)bz * g.part_ld + m0 + t] = v;
   }
 }
 
-template <bool BF16>
+template <bool BF16, int NP>
 __global__ __launch_bounds__(64 * kSmallWaves) __attribute__((amdgpu_waves_per_eu(1, 2)))
-void gemm_small_kernel(GemmMulti gm) {
+void gemm_small_kernel(GemmMulti<NP> gm) {
   extern __shared__ float small_lds[];
   int pi = 0;
-  while (pi + 1 < gm.n && (int)blockIdx.y >= gm.ty_end[pi]) ++pi;
-  const GemmArgs& g = gm.g[pi];
-  const int by = (int)blockIdx.y - (pi ? gm.ty_end[pi - 1] : 0);
-  if (g.skip && *g.skip) return;
-  if ((int)blockIdx.x * 32 >= g.N || by * 32 >= g.M || (int)blockIdx.z >= g.k_split) return;
+  while (pi + 1 < NP && (int)blockIdx.x >= gm.end[pi]) ++pi;
+  const GemmArgs& g = gm.g[NP == 1 ? 0 : pi];
+  const int id = (int)blockIdx.x - (pi ? gm.end[pi - 1] : 0);
+  const int tx = (g.N + 31) / 32, ty = (g.M + 31) / 32;
+  const int row = id / tx, bx = id - row * tx;
+  const int bz = row / ty, by = row - bz * ty;
   const bool sa = small_staged(g.lda_m, g.lda_k, g.M), sb = small_staged(g.ldb_n, g.ldb_k, g.N);
-  if (sa) {
-    if (sb) small_body<BF16, true, true>(g, by, small_lds);
-    else small_body<BF16, true, false>(g, by, small_lds);
-  } else {
-    if (sb) small_body<BF16, false, true>(g, by, small_lds);
-    else small_body<BF16, false, false>(g, by, small_lds);
-  }
+  auto body = [&](auto t) {
+    constexpr int T = decltype(t)::value;
+    if (sa) {
+      if (sb) small_body<BF16, true, true, T>(g, bx, by, bz, small_lds);
+      else small_body<BF16, true, false, T>(g, bx, by, bz, small_lds);
+    } else {
+      if (sb) small_body<BF16, false, true, T>(g, bx, by, bz, small_lds);
+      else small_body<BF16, false, false, T>(g, bx, by, bz, small_lds);
+    }
+  };
+  if (round_steps(small_steps_per_wave(g.K, g.k_split)) == 2) body(std::integral_constant<int, 2>{});
+  else body(std::integral_constant<int, 4>{});
 }
 
 template <bool BF16>
@@ -386,17 +426,18 @@ static hipError_t launch_gemm_t(const GemmArgs& g, const dim3& grid, hipStream_t
   return hipGetLastError();
 }
 
-template <bool BF16>
-static hipError_t launch_small_t(const GemmMulti& gm, const dim3& grid, size_t lds, hipStream_t s) {
+template <bool BF16, int NP>
+static hipError_t launch_small_t(const GemmMulti<NP>& gm, const dim3& grid, size_t lds,
+                                 hipStream_t s) {
   static bool lds_set = false;   // one attribute call per instantiation
   if (!lds_set) {
-    const int most = (int)((kSmallWaves * 64 + kSmallWaves * 2 * kStageFloats) * sizeof(float));
-    const hipError_t e = hipFuncSetAttribute((const void*)gemm_small_kernel<BF16>,
+    const int most = (int)((kSmallWaves * 64 + kSmallWaves * 2 * stage_floats(4)) * sizeof(float));
+    const hipError_t e = hipFuncSetAttribute((const void*)gemm_small_kernel<BF16, NP>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, most);
     if (e != hipSuccess) return e;
     lds_set = true;
   }
-  hipLaunchKernelGGL(gemm_small_kernel<BF16>, grid, dim3(64 * kSmallWaves), lds, s, gm);
+  hipLaunchKernelGGL((gemm_small_kernel<BF16, NP>), grid, dim3(64 * kSmallWaves), lds, s, gm);
   return hipGetLastError();
 }
 
@@ -417,27 +458,31 @@ static hipError_t check_gemm(GemmArgs& g, bool* small) {
   return hipSuccess;
 }
 
-hipError_t launch_gemm_multi(const GemmArgs* gs, int n, bool bf16, hipStream_t s) {
-  if (n < 1 || n > kMaxProducts) return hipErrorInvalidValue;
-  GemmMulti gm{};
-  gm.n = n;
-  int tx = 0, ty = 0, tz = 1;
+template <int NP>
+static hipError_t launch_products(const GemmArgs* gs, bool bf16, hipStream_t s) {
+  GemmMulti<NP> gm{};
+  int groups = 0;
   size_t lds = 0;
-  for (int p = 0; p < n; ++p) {
+  for (int p = 0; p < NP; ++p) {
     GemmArgs g = gs[p];
     bool small = false;
     const hipError_t e = check_gemm(g, &small);
     if (e != hipSuccess) return e;
     if (!small) return hipErrorInvalidValue;
     gm.g[p] = g;
-    tx = std::max(tx, (g.N + 31) / 32);
-    ty += (g.M + 31) / 32;
-    gm.ty_end[p] = ty;
-    tz = std::max(tz, g.k_split);
+    groups += (g.N + 31) / 32 * ((g.M + 31) / 32) * g.k_split;
+    gm.end[p] = groups;
     lds = std::max(lds, small_lds_bytes(g));
   }
-  const dim3 grid(tx, ty, tz);
-  return bf16 ? launch_small_t<true>(gm, grid, lds, s) : launch_small_t<false>(gm, grid, lds, s);
+  const dim3 grid(groups);
+  return bf16 ? launch_small_t<true, NP>(gm, grid, lds, s)
+              : launch_small_t<false, NP>(gm, grid, lds, s);
+}
+
+hipError_t launch_gemm_multi(const GemmArgs* gs, int n, bool bf16, hipStream_t s) {
+  if (n == 1) return launch_products<1>(gs, bf16, s);
+  if (n == kMaxProducts) return launch_products<kMaxProducts>(gs, bf16, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm(const GemmArgs& g0, bool bf16, hipStream_t s) {
@@ -461,12 +506,10 @@ __global__ __launch_bounds__(256) void out_layer_kernel(const float* H2, const f
                                                         const float* t, const float* Z2, float* dy,
                                                         float* dZ2, int32_t* step,
                                                         const int32_t* skip) {
-  if (skip && *skip) return;
-  if (step && blockIdx.x == 0 && threadIdx.x == 0) *step += 1;
+  const int32_t skipped = skip ? *skip : 0;   // tested under the loads
   const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (b >= B) return;
-  const float* h = H2 + (int64_t)b * H;
+  const float* h = H2 + (int64_t)min(b, B - 1) * H;
   constexpr int kRow = 8;   // up to 512 units: the row's values stay in registers
   if (H <= 64 * kRow) {
     // Every load (H2, w3, Z2, t) issued before the first use: one memory
@@ -477,15 +520,20 @@ __global__ __launch_bounds__(256) void out_layer_kernel(const float* H2, const f
       const int j = min(lane + 64 * u, H - 1);
       hv[u] = h[j];
       wv[u] = w3[j];
-      zv[u] = t ? Z2[(int64_t)b * H + j] : 0.f;
+      zv[u] = t ? Z2[(int64_t)min(b, B - 1) * H + j] : 0.f;
     }
-    const float tb = t ? t[b] : 0.f;
+    const float tb = t ? t[min(b, B - 1)] : 0.f;
+    const float bias = b3[0];
+    __builtin_amdgcn_sched_barrier(0);
+    if (skipped) return;
+    if (step && blockIdx.x == 0 && threadIdx.x == 0) *step += 1;
+    if (b >= B) return;
     float acc = 0.f;
 #pragma unroll
     for (int u = 0; u < kRow; ++u)
       if (lane + 64 * u < H) acc = fmaf(hv[u], wv[u], acc);
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    const float yb = acc + b3[0];
+    const float yb = acc + bias;
     if (lane == 0) y[b] = yb;
     if (!t) return;
     const float d = 2.f * (yb - tb) / (float)B;
@@ -495,6 +543,9 @@ __global__ __launch_bounds__(256) void out_layer_kernel(const float* H2, const f
       if (lane + 64 * u < H) dZ2[(int64_t)b * H + lane + 64 * u] = d * wv[u] * gelu_grad_f(zv[u]);
     return;
   }
+  if (skipped) return;
+  if (step && blockIdx.x == 0 && threadIdx.x == 0) *step += 1;
+  if (b >= B) return;
   float acc = 0.f;
   for (int j = lane; j < H; j += 64) acc = fmaf(h[j], w3[j], acc);
   for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
@@ -523,9 +574,8 @@ hipError_t launch_out_layer(const float* H2, const float* w3, const float* b3, i
 // advanced it.
 __global__ void adam_kernel(float* p, const float* part, int ks, float* m, float* v, int64_t n,
                             float lr, const SurrogateState* st, const int32_t* skip) {
-  if (skip && *skip) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) adam_update(p, part, ks, m, v, n, lr, st->step, i);
+  if (i < n) adam_update(p, part, ks, m, v, n, lr, st->step, i, skip ? *skip : 0);
 }
 
 hipError_t launch_adam(float* p, const float* part, int ks, float* m, float* v, int64_t n,

@@ -323,3 +323,12 @@ def test_screened_run_equals_screened_steps(gg, precision):
         g.close()
         s.close()
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("fp32", [True, False])
+@pytest.mark.parametrize("n_in,H,B", [(256, 33, 31), (257, 32, 257), (31, 300, 511), (33, 256, 513),
+                                      (2, 1, 1), (128, 129, 1024)])
+def test_products_at_round_edges(gg, fp32, n_in, H, B):
+    """Products whose waves take one round of 2 steps (K up to 256) or rounds
+    of 4, with tiles, k blocks and minibatch ranges whole and ragged."""
+    test_forward_and_gradients_match_oracle(gg, fp32, n_in, H, B)
