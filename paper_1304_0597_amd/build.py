@@ -23,14 +23,14 @@ LIB = os.path.join(HERE, "libgame.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 SOURCES = ["fitness_f32.hip", "fitness_bf16.hip", "rescore64.hip", "batch.hip", "mlp.hip",
-           "ga.hip", "predict.hip", "trig_sums.hip", "runtime.hip"]
+           "ga.hip", "resident.hip", "predict.hip", "trig_sums.hip", "runtime.hip"]
 COMMON = ["-O3", f"--offload-arch={ARCH}", "-std=c++20", "-fPIC",
           # keep the compiler from emitting packed-FP32 VALU instructions
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-I", os.path.join(ROOT, "include"), "-Wno-unused-command-line-argument"]
 # The genetic operators must round every float step on its own so that they
 # reproduce the same bits as the float32 reference arithmetic.
-PER_FILE = {"ga.hip": ["-ffp-contract=off"]}
+PER_FILE = {"ga.hip": ["-ffp-contract=off"], "resident.hip": ["-ffp-contract=off"]}
 
 
 def _compile(src: str) -> str:

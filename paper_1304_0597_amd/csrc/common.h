@@ -263,6 +263,11 @@ struct CompactArgs {
 bool compact_fits(int P, int K, int k, int selection);
 int compact_blocks(int k, int selection);
 hipError_t launch_compact_tail(CompactArgs a, hipStream_t s);
+// Up to `generations` generations of a run in one launch (see resident.hip),
+// for the runs whose plan f and genetic step g resident_fits accepts.
+bool resident_fits(const FitArgs& f, const GAArgs& g);
+hipError_t launch_resident(const FitArgs& f, const GAArgs& g, const RankArgs& r, int generations,
+                           hipStream_t s);
 // With zero set, also clears n_zero words there.
 hipError_t launch_set_state(RunState* st, int32_t gen, int32_t max_gen, double target,
                             int32_t reset, hipStream_t s, unsigned long long* zero = nullptr,

@@ -10,31 +10,31 @@ struct U64x4 {
   uint64_t o0, o1, o2, o3;
 };
 
-// The 128-bit products are formed once each (four 32-bit multiply-adds); a
-// low product and a high product of their own take six.
-__device__ __forceinline__ U64x4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3,
-                                               uint64_t k0, uint64_t k1) {
+// Rounds R0 .. R1 - 1 of counter c under key (k0, k1).  The 128-bit products
+// are formed once each (four 32-bit multiply-adds); a low product and a high
+// product of their own take six.
+template <int R0, int R1>
+__device__ __forceinline__ U64x4 philox_rounds(U64x4 c, uint64_t k0, uint64_t k1) {
   constexpr uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
   constexpr uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
+  k0 += R0 * W0;
+  k1 += R0 * W1;
 #pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r) {
+  for (int r = R0; r < R1; ++r) {
+    if (r > R0) {
       k0 += W0;
       k1 += W1;
     }
-    const unsigned __int128 p0 = (unsigned __int128)M0 * c0, p1 = (unsigned __int128)M1 * c2;
-    const uint64_t n0 = (uint64_t)(p1 >> 64) ^ c1 ^ k0, n2 = (uint64_t)(p0 >> 64) ^ c3 ^ k1;
-    c0 = n0;
-    c1 = (uint64_t)p1;
-    c2 = n2;
-    c3 = (uint64_t)p0;
+    const unsigned __int128 p0 = (unsigned __int128)M0 * c.o0, p1 = (unsigned __int128)M1 * c.o2;
+    const uint64_t n0 = (uint64_t)(p1 >> 64) ^ c.o1 ^ k0, n2 = (uint64_t)(p0 >> 64) ^ c.o3 ^ k1;
+    c = {n0, (uint64_t)p1, n2, (uint64_t)p0};
   }
-  return {c0, c1, c2, c3};
+  return c;
 }
 
 __device__ __forceinline__ U64x4 draw(uint64_t seed, uint64_t stream, uint64_t gen, uint64_t unit,
                                       uint64_t blk) {
-  return philox4x64_10(gen, unit, blk, 0, seed, stream);
+  return philox_rounds<0, 10>({gen, unit, blk, 0}, seed, stream);
 }
 
 __device__ __forceinline__ float gauss12(const U64x4& b) {

@@ -534,6 +534,30 @@ int enqueue_tail(game_ctx* h, hipStream_t s) {
   return GAME_OK;
 }
 
+RankArgs rank_args(const game_ctx* h, const FitArgs& fa) {
+  RankArgs ra{};
+  ra.partial = h->partial;
+  ra.n_splits = fa.n_splits;
+  ra.ld_partial = fa.ld_partial;
+  ra.NP = h->NP;
+  ra.P = h->cfg.population;
+  ra.error_fn = h->cfg.error_fn;
+  ra.fit32 = h->fit32;
+  ra.fit64 = h->fit64;
+  ra.order = h->order;
+  ra.state = h->state;
+  return ra;
+}
+
+// Generations per launch of a resident run: some milliseconds.
+constexpr int kResidentGenerations = 1024;
+
+// Whether game_run takes the resident kernel.
+bool resident_run(const game_ctx* h) {
+  return h->cfg.precision == GAME_FP32 &&
+         resident_fits(fit_args(h, h->X, h->t, h->NP, h->pop[0], h->cfg.population), step_args(h));
+}
+
 // One generation of the loop on stream s: evaluate pop[gen & 1], finish and
 // rank, stop test, then build pop[(gen + 1) & 1].
 // With `live` (a compact run's game_run) the population being evaluated is
@@ -569,17 +593,7 @@ int enqueue_step(game_ctx* h, hipStream_t s, bool live = false) {
     d.n_items = d.n_pairs * d.blocks + d.P * d.K;
   }
   GAME_HIP(launch_fitness(h, fa, s));
-  RankArgs ra{};
-  ra.partial = h->partial;
-  ra.n_splits = fa.n_splits;
-  ra.ld_partial = fa.ld_partial;
-  ra.NP = h->NP;
-  ra.P = h->cfg.population;
-  ra.error_fn = h->cfg.error_fn;
-  ra.fit32 = h->fit32;
-  ra.fit64 = h->fit64;
-  ra.order = h->order;
-  ra.state = h->state;
+  const RankArgs ra = rank_args(h, fa);
   if (compact) {
     CompactArgs ca{};
     ca.rank = ra;
@@ -943,6 +957,18 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
                                     const int r = enqueue_step(h, h->stream);
                                     if (r) return r;
                                   }
+                                  return (int)GAME_OK;
+                                });
+    if (rc) return rc;
+  } else if (!st.stop && resident_run(h)) {
+    const FitArgs fa = fit_args(h, h->X, h->t, h->NP, h->pop[0], h->cfg.population);
+    int64_t left = evals;
+    const int rc = queue_chunks(h->stream, (evals + kResidentGenerations - 1) / kResidentGenerations,
+                                h->state, 1, h->host_state, h->chunk_done, [&]() {
+                                  const int n = (int)std::min<int64_t>(left, kResidentGenerations);
+                                  left -= n;
+                                  GAME_HIP(launch_resident(fa, step_args(h), rank_args(h, fa), n,
+                                                           h->stream));
                                   return (int)GAME_OK;
                                 });
     if (rc) return rc;

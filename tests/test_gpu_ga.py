@@ -361,3 +361,58 @@ def test_generation_tail_at_its_edges(gg, case):
     assert gens == 3
     assert np.array_equal(bits(g.population()[0].cpu().numpy()), bits(nxt))
     g.close()
+
+
+@pytest.mark.parametrize("case", [
+    # (NP, N, d, basis, P, generations): ends of 64-row units and 256-row tiles,
+    # one and two column tiles, an odd last feature, 1 to 30 tiles, more genes
+    # than threads, more generations than a launch, every basis and option
+    (1, 1, 1, 0, 2, 3, {}), (64, 3, 2, 1, 32, 9, dict(selection=1)),
+    (65, 2, 3, 3, 33, 9, dict(selection=2, elitism=0)),
+    (256, 5, 1, 2, 64, 9, dict(error_fn=2)), (257, 4, 2, 3, 63, 9, dict(error_fn=1, elitism=5)),
+    (2100, 8, 1, 2, 23, 1030, dict(error_fn=2)), (300, 7, 4, 0, 50, 9, dict(elite_mode=1)),
+    (7500, 2, 1, 2, 5, 9, dict(tournament_k=5)), (4096, 1, 1, 2, 5, 9, dict(error_fn=3)),
+    (100, 31, 1, 1, 40, 9, dict(tournament_k=7, p_mutation=1.0))],
+    ids=lambda c: "x".join(map(str, c[:6])) + "-" + "-".join(f"{k}{v}" for k, v in c[6].items()))
+def test_whole_runs_equal_their_generations(gg, case):
+    """game_run ends with the bits that game_step reaches, on a first run, a
+    continued one and one stopped by its target."""
+    NP, N, d, basis, P, gens, kw = case
+    rng = np.random.default_rng(NP + P)
+    X = torch.from_numpy(rng.uniform(-1, 1, (NP, N)).astype(np.float32)).cuda()
+    t = torch.from_numpy((rng.random(NP) < 0.5).astype(np.float32)).cuda()
+    kw = dict(dict(tournament_k=min(3, P), elitism=min(2, P - 1)), **kw)
+    c = gg.config(basis=basis, degree=d, population=P, seed=5, max_generations=gens, target=-1.0,
+                  **kw)
+    a, b = gg.Game(c, X, t), gg.Game(c, X, t)
+
+    def same():
+        (pa, fa), (pb, fb) = a.population(), b.population()
+        assert np.array_equal(bits(pa.cpu().numpy()), bits(pb.cpu().numpy()))
+        assert np.array_equal(bits(fa.cpu().numpy()), bits(fb.cpu().numpy()))
+
+    a.init_population()
+    b.init_population()
+    done, _, _ = a.run()
+    for _ in range(gens + 1):
+        b.step()
+    assert done == gens and a.state() == b.state()
+    same()
+    done, _, _ = a.run(max_generations=gens + 4)
+    assert done == gens + 4
+    # the continued run again, from the evaluated population by steps
+    e = gg.Game(gg.config(basis=basis, degree=d, population=P, seed=5, max_generations=gens + 4,
+                          target=-1.0, **kw), X, t)
+    e.set_population(b.population()[0], gens)
+    for _ in range(5):
+        e.step()
+    (pa, fa), (pe, fe) = a.population(), e.population()
+    assert np.array_equal(bits(pa.cpu().numpy()), bits(pe.cpu().numpy()))
+    assert np.array_equal(bits(fa.cpu().numpy()), bits(fe.cpu().numpy()))
+    # a target that the first population meets
+    a.init_population()
+    done, _, _ = a.run(target=1e30)
+    assert done == 0 and a.state()["stopped"]
+    a.close()
+    b.close()
+    e.close()
