@@ -627,8 +627,31 @@ hipError_t launch_copy_current(const RunState* st, const float* pop0, const floa
   return hipGetLastError();
 }
 
+// Run states, and with K set the best chromosome of the one run (float32 genes
+// of its evaluated population), written to pinned host memory from a kernel:
+// a device-to-host copy of these few bytes goes through a copy engine, which
+// leaves the stream idle for 20-30 us.
+__global__ void publish_kernel(const RunState* st, int n, RunState* slots, const float* pop0,
+                               const float* pop1, int32_t K, float* genes) {
+  constexpr int kStateWords = sizeof(RunState) / sizeof(uint32_t);
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(st);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(slots);
+  for (int i = threadIdx.x; i < n * kStateWords; i += blockDim.x) dst[i] = src[i];
+  if (K && st->best >= 0) {
+    const float* best = ((st->gen & 1) ? pop1 : pop0) + (int64_t)st->best * K;
+    for (int i = threadIdx.x; i < K; i += blockDim.x) genes[i] = best[i];
+  }
+}
+
+hipError_t launch_publish(const RunState* st, int n, RunState* slots, hipStream_t s,
+                          const float* pop0 = nullptr, const float* pop1 = nullptr, int32_t K = 0,
+                          float* genes = nullptr) {
+  hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(256), 0, s, st, n, slots, pop0, pop1, K, genes);
+  return hipGetLastError();
+}
+
 // Queues up to n_chunks chunks of generations (enqueue() queues one) with
-// two chunks in flight: after each chunk the n run states are copied to one
+// two chunks in flight: after each chunk the n run states are written to one
 // of two pinned host slots and an event is recorded; before queuing chunk i
 // the host waits for chunk i - 2's copy and stops queuing once every run had
 // stopped by then.  Chunks queued after a stop do nothing (every kernel reads
@@ -646,17 +669,19 @@ int queue_chunks(hipStream_t s, int64_t n_chunks, const RunState* dev, int n, Ru
     }
     const int rc = enqueue();
     if (rc) return rc;
-    GAME_HIP(hipMemcpyAsync(slot, dev, sizeof(RunState) * n, hipMemcpyDeviceToHost, s));
+    GAME_HIP(launch_publish(dev, n, slot, s));
     GAME_HIP(hipEventRecord(done[i & 1], s));
   }
   return GAME_OK;
 }
 
-// Pinned host slots and events for queue_chunks over n run states.
-int create_chunk_sync(int n, RunState** slots, hipEvent_t* done) {
+// Pinned host slots and events for queue_chunks over n run states, and K
+// pinned floats after the slots.
+int create_chunk_sync(int n, int32_t K, RunState** slots, hipEvent_t* done) {
   *slots = nullptr;
   done[0] = done[1] = nullptr;
-  GAME_HIP(hipHostMalloc((void**)slots, 2 * sizeof(RunState) * n, hipHostMallocDefault));
+  GAME_HIP(hipHostMalloc((void**)slots, 2 * sizeof(RunState) * n + sizeof(float) * K,
+                         hipHostMallocDefault));
   for (int i = 0; i < 2; ++i)
     GAME_HIP(hipEventCreateWithFlags(&done[i], hipEventDisableTiming));
   return GAME_OK;
@@ -763,7 +788,7 @@ int game_create(const game_config* c, const float* X, const float* t, int64_t NP
     delete h;
     return hip_fail(e, "hipStreamCreateWithFlags");
   }
-  rc = create_chunk_sync(1, &h->host_state, h->chunk_done);
+  rc = create_chunk_sync(1, h->K, &h->host_state, h->chunk_done);
   if (rc == GAME_OK) {
     e = launch_set_state(h->state, 0, c->max_generations, c->target, 1, h->stream, h->tally,
                          kTallyBytes / sizeof(uint64_t));
@@ -924,9 +949,9 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
   if (!h->initialized) return fail(GAME_ESTATE, "population not initialised");
   if (max_gen >= 0) h->cfg.max_generations = max_gen;
   if (target >= 0) h->cfg.target = target;
-  RunState st{};
-  GAME_HIP(hipMemcpyAsync(&st, h->state, sizeof st, hipMemcpyDeviceToHost, h->stream));
+  GAME_HIP(launch_publish(h->state, 1, h->host_state, h->stream));
   GAME_HIP(hipStreamSynchronize(h->stream));
+  RunState st = *h->host_state;
   // A run stopped on its last evaluation continues from it when that
   // evaluation meets neither new criterion: the stop test's other branch
   // (the counter advances), then the rest of that generation, exactly as
@@ -1001,9 +1026,10 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
     }
     // Two replays (16 generations) per chunk.
     const int64_t launches = (evals + h->graph_steps - 1) / h->graph_steps;
+    int64_t left = launches;
     const int rc = queue_chunks(h->stream, (launches + 1) / 2, h->state, 1, h->host_state,
                                 h->chunk_done, [&]() {
-                                  for (int i = 0; i < 2; ++i) {
+                                  for (int i = 0; i < 2 && left > 0; ++i, --left) {
                                     const hipError_t e = hipGraphLaunch(h->graph, h->stream);
                                     if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
                                   }
@@ -1011,8 +1037,11 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
                                 });
     if (rc) return rc;
   }
-  GAME_HIP(hipMemcpyAsync(&st, h->state, sizeof st, hipMemcpyDeviceToHost, h->stream));
+  float* genes = reinterpret_cast<float*>(h->host_state + 2);
+  GAME_HIP(launch_publish(h->state, 1, h->host_state, h->stream, h->pop[0], h->pop[1],
+                          best_genes ? h->K : 0, genes));
   GAME_HIP(hipStreamSynchronize(h->stream));
+  st = *h->host_state;
   if (gens_done) *gens_done = st.gen;
   if (best_err) *best_err = st.best_err;
   if (st.best >= 0 && h->cfg.precision != GAME_FP32) {
@@ -1024,12 +1053,7 @@ int game_run(game_t h, int32_t max_gen, double target, int32_t* gens_done, float
     GAME_HIP(hipStreamSynchronize(h->stream));
     if (best_err) *best_err = v;
   }
-  if (best_genes && st.best >= 0) {
-    const float* src = h->pop[st.gen & 1] + (int64_t)st.best * h->K;
-    GAME_HIP(hipMemcpyAsync(best_genes, src, sizeof(float) * h->K, hipMemcpyDeviceToHost,
-                            h->stream));
-    GAME_HIP(hipStreamSynchronize(h->stream));
-  }
+  if (best_genes && st.best >= 0) std::copy_n(genes, h->K, best_genes);
   return GAME_OK;
 }
 
@@ -1714,7 +1738,7 @@ int game_batch_create(const game_run_desc* runs, int32_t n_runs, void* ws, size_
     e = launch_trig_cs(r.X, r.NP, r.N, const_cast<float*>(r.cs), b->stream);
     if (e != hipSuccess) rc = hip_fail(e, "launch_trig_cs");
   }
-  if (!rc) rc = create_chunk_sync(n_runs, &b->host_states, b->chunk_done);
+  if (!rc) rc = create_chunk_sync(n_runs, 0, &b->host_states, b->chunk_done);
   if (!rc) rc = build_items(b, 8);
   if (rc) {
     destroy_chunk_sync(b->host_states, b->chunk_done);
@@ -1948,9 +1972,10 @@ int game_batch_run(game_batch_t b, int32_t* gens_done, double* best_err) {
     // Two replays (8 generations) per chunk, until every run has stopped.
     const int64_t evals = std::max<int64_t>(1, (int64_t)b->max_gen - min_gen + 1);
     const int64_t launches = (evals + b->graph_steps - 1) / b->graph_steps;
+    int64_t left = launches;
     const int rc = queue_chunks(b->stream, (launches + 1) / 2, b->states, b->n_runs,
                                 b->host_states, b->chunk_done, [&]() {
-                                  for (int i = 0; i < 2; ++i) {
+                                  for (int i = 0; i < 2 && left > 0; ++i, --left) {
                                     const hipError_t e = hipGraphLaunch(b->graph, b->stream);
                                     if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
                                   }
