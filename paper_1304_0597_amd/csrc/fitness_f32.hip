@@ -53,8 +53,12 @@
 
 namespace game {
 
-template <int BASIS, int D, int CB>
-__global__ __launch_bounds__(64 * fit_waves(CB), 8 / fit_waves(CB)) void fitness_f32_kernel(FitArgs a) {
+// ROWS: the general tile body, or the one for narrow rows, single features or
+// whole quads at a time.
+enum { kGeneralRows, kNarrowRows, kNarrowQuads };
+template <int BASIS, int D, int CB, int ROWS>
+__global__ __launch_bounds__(64 * fit_waves(CB), (ROWS && CB == 1 ? 16 : 8) / fit_waves(CB)) void
+fitness_f32_kernel(FitArgs a) {
   extern __shared__ float lds[];
   const int total = a.n_ctiles * a.n_splits;
   const int b = blockIdx.x;
@@ -77,25 +81,39 @@ __global__ __launch_bounds__(64 * fit_waves(CB), 8 / fit_waves(CB)) void fitness
   const int L = xcd * (total >> 3) + min(xcd, total & 7) + (b >> 3);
   const int split = L / a.n_ctiles;
   const int ctile = L - split * a.n_ctiles;
-  fitness_f32_block<BASIS, D, CB>(a, genes, split, ctile, lds, a.stop);
+  if constexpr (ROWS == kGeneralRows)
+    fitness_f32_block<BASIS, D, CB>(a, genes, split, ctile, lds, a.stop);
+  else
+    fitness_f32_narrow<BASIS, D, CB, ROWS == kNarrowQuads>(a, genes, split, ctile, lds, a.stop);
   if (b == 0 && threadIdx.x == 0) {
     if (a.stop_seen) *a.stop_seen = *a.stop;
     if (a.gen_seen) *a.gen_seen = *a.gen_sel;
   }
 }
 
-template <int BASIS, int D, int CB>
-static hipError_t launch_cb(const FitArgs& a, hipStream_t s) {
-  const size_t lds = fitness_lds_bytes(a, D);
+template <int BASIS, int D, int CB, int ROWS>
+static hipError_t launch_rows(const FitArgs& a, hipStream_t s) {
+  const size_t lds = ROWS ? fit_waves(CB) * 32 * CB * sizeof(double) : fitness_lds_bytes(a, D);
   const int threads = 64 * fit_waves(CB);
   const int grid = a.n_ctiles * a.n_splits + (a.draw.n_items + threads - 1) / threads;
   if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute((const void*)fitness_f32_kernel<BASIS, D, CB>,
+    const hipError_t e = hipFuncSetAttribute((const void*)fitness_f32_kernel<BASIS, D, CB, ROWS>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((fitness_f32_kernel<BASIS, D, CB>), dim3(grid), dim3(threads), lds, s, a);
+  hipLaunchKernelGGL((fitness_f32_kernel<BASIS, D, CB, ROWS>), dim3(grid), dim3(threads), lds, s, a);
   return hipGetLastError();
+}
+
+template <int BASIS, int D, int CB>
+static hipError_t launch_cb(const FitArgs& a, hipStream_t s) {
+  if constexpr (BASIS < 3 && narrow_degree(D) && CB <= 2) {
+    if (a.Q <= pairs_ahead(D, CB))
+      return a.N % 4 == 0 && reinterpret_cast<uintptr_t>(a.X) % 16 == 0
+                 ? launch_rows<BASIS, D, CB, kNarrowQuads>(a, s)
+                 : launch_rows<BASIS, D, CB, kNarrowRows>(a, s);
+  }
+  return launch_rows<BASIS, D, CB, kGeneralRows>(a, s);
 }
 
 template <int BASIS, int D>

@@ -263,15 +263,16 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
   for (int i = 0; i < QP; ++i)
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) xn[i][rb] = sn[i][rb] = 0.f;
-  // Minus the targets of the wave's rows (0 past the data); at low degree
-  // they are read a tile ahead too.
+  // The targets of the wave's rows (0 past the data), negated at their use so
+  // that nothing waits for them here; at low degree they are read a tile ahead
+  // too.
   constexpr bool kTargetsAhead = QP >= 4;
   float tn[RB];
   auto load_t = [&](int tile, float (&to)[RB]) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const int64_t r = row_of(tile, rb);
-      to[rb] = (RB == 2 || tile + rb / 2 < tile_end) && r < NP ? -global_f32(a.t)[r] : 0.f;
+      to[rb] = (RB == 2 || tile + rb / 2 < tile_end) && r < NP ? global_f32(a.t)[r] : 0.f;
     }
   };
 #pragma unroll
@@ -284,6 +285,7 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's copies landed
     __syncthreads();
   }
+  if (stopped) return;
 
   // Chunked genes: stage index st runs over (tile, chunk) in loop order and
   // uses buffer st & 1.
@@ -413,7 +415,7 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
     // Out - t (0 for rows past the data).
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      const float ab = h ? nt[rb] : (row_ok[rb] ? 1.f : 0.f);
+      const float ab = h ? -nt[rb] : (row_ok[rb] ? 1.f : 0.f);
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb)
         acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(ab, h ? 1.f : w0[cb], acc[rb][cb], 0, 0, 0);
@@ -470,5 +472,183 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
   }
 }
 
+
+// Whether rows of Q feature pairs at degree D are narrow: one group of pairs.
+__host__ __device__ constexpr bool narrow_degree(int d) { return d <= 4; }
+
+// The same tile for narrow rows (Q <= pairs_ahead(D, CB), degree <= 4, no sine and
+// cosine): all features of a row are one group, read a tile ahead, and a lane's
+// genes stay in registers, so the loop over tiles touches neither LDS nor
+// launch parameters.  float32 products run at the vector rate, so every vector
+// instruction beside them counts: the general loop issued 385 a tile of 64 rows
+// (60 to keep its bounds and addresses in vector lanes, 63 to clear and move
+// accumulators) besides 18 products, this one NARROW_COUNT.
+// QUADS: rows are whole aligned 16-byte quads, read one per lane and load.
+template <int BASIS, int D, int CB, bool QUADS>
+__device__ __forceinline__ void fitness_f32_narrow(const FitArgs& a_in,
+                                                   const float* __restrict__ genes, int split,
+                                                   int ctile, float* lds, const int32_t* stop) {
+  static_assert(BASIS >= 0 && BASIS <= 2 && narrow_degree(D) && CB <= 2, "narrow rows");
+  const int32_t stopped = stop ? *stop : 0;
+  constexpr int QP = pairs_ahead(D, CB);
+  constexpr int RB = 2;
+  constexpr int kCols = 32 * CB;
+  const gptr_f32 X = global_f32(uniform(a_in.X)), t = global_f32(uniform(a_in.t));
+  const gptr_f32 G = global_f32(uniform(genes));
+  const int64_t NP = uniform(a_in.NP);
+  const int N = uniform(a_in.N), K = uniform(a_in.K), Q = uniform(a_in.Q);
+  const int n_chrom = uniform(a_in.n_chrom), error_fn = uniform(a_in.error_fn);
+  const float R = uniform(a_in.R);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m = lane & 31, h = lane >> 5;
+  const int c0 = ctile * kCols;
+  const int tile_begin = split * uniform(a_in.tiles_per_split);
+  const int tile_end = min(tile_begin + uniform(a_in.tiles_per_split), uniform(a_in.n_tiles));
+
+  // The features of the lane's rows of a tile (0 outside the data) and their
+  // targets.
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef const f32x4 __attribute__((address_space(1)))* gptr_f32x4;
+  float xn[QP][RB], tn[RB];
+  auto load = [&](int tile) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int64_t r = (int64_t)tile * kTileRows + wave * 64 + rb * 32 + m;
+      const bool ok = r < NP;
+      if constexpr (QUADS) {
+        // Half h reads quads 2 k + h; the halves' words are exchanged at their use.
+        const gptr_f32x4 src = (gptr_f32x4)(X + r * N) + h;
+#pragma unroll
+        for (int k = 0; k < QP / 4; ++k) {
+          f32x4 v = {0.f, 0.f, 0.f, 0.f};
+          if (ok && 8 * k + 4 * h < N) v = src[2 * k];
+          xn[4 * k][rb] = v.x;
+          xn[4 * k + 1][rb] = v.y;
+          xn[4 * k + 2][rb] = v.z;
+          xn[4 * k + 3][rb] = v.w;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < QP; ++i) xn[i][rb] = ok && 2 * i + h < N ? X[r * N + 2 * i + h] : 0.f;
+      }
+      tn[rb] = ok ? t[r] : 0.f;           // (negated at its use: no wait here)
+    }
+  };
+  if (tile_begin < tile_end) load(tile_begin);
+  // Genes of this lane's columns: pair i, degree j; zero past the features.
+  float b[QP * D][CB], w0[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) {
+    const gptr_f32 g = G + (int64_t)min(c0 + cb * 32 + m, n_chrom - 1) * K;
+    w0[cb] = g[0];
+#pragma unroll
+    for (int i = 0; i < QP; ++i)
+#pragma unroll
+      for (int j = 0; j < D; ++j)
+        b[i * D + j][cb] = 2 * i + h < N ? g[1 + (2 * i + h) * D + j] : 0.f;
+  }
+  if (stopped) return;
+
+  double acc64[CB];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) acc64[cb] = 0.0;
+  for (int tile = tile_begin; tile < tile_end; ++tile) {
+    float x[QP][RB], nt[RB];
+    bool row_ok[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      row_ok[rb] = (int64_t)tile * kTileRows + wave * 64 + rb * 32 + m < NP;
+      nt[rb] = tn[rb];
+      if constexpr (QUADS) {
+#pragma unroll
+        for (int k = 0; k < QP; k += 4) {
+          swap_halves(xn[k][rb], xn[k + 1][rb], x[k][rb], x[k + 2][rb]);
+          swap_halves(xn[k + 2][rb], xn[k + 3][rb], x[k + 1][rb], x[k + 3][rb]);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < QP; ++i) x[i][rb] = xn[i][rb];
+      }
+    }
+    if (tile + 1 < tile_end) load(tile + 1);
+    f32x16 acc[RB][CB];
+    auto pair = [&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      Recur<BASIS> rc[RB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        rc[rb].seed(x[i][rb], h);
+        // (a power of a zero is zero by itself)
+        if constexpr (D > 1 && BASIS != 2) zero_chain(rc[rb], row_ok[rb]);
+      }
+      auto kstep = [&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) {
+            if constexpr (i == 0 && j == 0)
+              acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(rc[rb].cur, b[0][cb], f32x16{}, 0, 0, 0);
+            else
+              acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(rc[rb].cur, b[i * D + j][cb],
+                                                                 acc[rb][cb], 0, 0, 0);
+          }
+        if constexpr (j + 1 < D) {
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) rc[rb].template advance<j + 1>(x[i][rb]);
+        }
+      };
+      [&]<int... J>(std::integer_sequence<int, J...>) {
+        (kstep(std::integral_constant<int, J>{}), ...);
+      }(std::make_integer_sequence<int, D>{});
+    };
+    pair(std::integral_constant<int, 0>{});
+    [&]<int... I>(std::integer_sequence<int, I...>) {
+      ((I + 1 < Q && (pair(std::integral_constant<int, I + 1>{}), true)) && ...);
+    }(std::make_integer_sequence<int, QP - 1>{});
+    // Bias and target step, error terms: as in fitness_f32_block.
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const float ab = h ? -nt[rb] : (row_ok[rb] ? 1.f : 0.f);
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+        acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(ab, h ? 1.f : w0[cb], acc[rb][cb], 0, 0, 0);
+    }
+    float s[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) s[cb] = 0.f;
+    auto epilogue = [&](auto mode_c) {
+      constexpr int mode = decltype(mode_c)::value;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) s[cb] = add_error_term<mode>(s[cb], acc[rb][cb][i], R);
+    };
+    if (error_fn == 2) epilogue(std::integral_constant<int, 2>{});
+    else if (error_fn == 3) epilogue(std::integral_constant<int, 3>{});
+    else epilogue(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) acc64[cb] += (double)s[cb];
+  }
+
+  // Lane halves, then the waves, in the order of fitness_f32_block.
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb) acc64[cb] += __shfl_xor(acc64[cb], 32);
+  double* red = reinterpret_cast<double*>(lds);
+  if (h == 0) {
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) red[wave * kCols + cb * 32 + m] = acc64[cb];
+  }
+  __syncthreads();
+  if (threadIdx.x < kCols) {
+    const int c = threadIdx.x;
+    double v = red[c];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v += red[w * kCols + c];
+    a_in.partial[(int64_t)split * a_in.ld_partial + c0 + c] = v;
+  }
+}
 
 }  // namespace game
