@@ -42,7 +42,8 @@
 //    the features of several pairs, and the targets, are loaded a group (a
 //    tile) ahead, and rows of whole 16-byte quads a quad per lane and load.
 //    7,168,000 x 16 patterns, degree 1, 23 chromosomes (TMSE): 347 us before,
-//    172 now (2.8 TB/s; MFMAs and epilogue take about half of it).
+//    172 so, and 130 in the loop of its own that narrow rows have
+//    (fitness_f32_narrow).
 //  * Grid: (pattern split) x (chromosome tile); consecutive blocks of one
 //    split are mapped onto one XCD so its L2 serves the split's rows to all
 //    chromosome tiles.
@@ -193,8 +194,11 @@ void plan_fitness(FitArgs& a, int degree, int basis, bool wide) {
     const int ctiles = (a.n_chrom + 32 * cb - 1) / (32 * cb);
     const int streams = cb == 4 ? 2 : 1;
     // As many workgroups per CU as fit (few terms need the most reads in
-    // flight), or fewer when that saves more than 3 %.
-    const int most = cb == 4 ? 1 : cb == 2 ? 2 : a.Q * degree <= 16 ? 8 : 4;
+    // flight: 8 are two rounds of 4), or fewer when that saves more than 3 %.
+    // Narrow rows keep their genes in registers, and one round reads them once:
+    // 7,168,000 x 16 in 1,024 workgroups 136 us, in 2,048 147.
+    const bool narrow = basis < 3 && narrow_degree(degree) && a.Q <= pairs_ahead(degree, cb);
+    const int most = cb == 4 ? 1 : cb == 2 ? 2 : a.Q * degree <= 16 && !narrow ? 8 : 4;
     int64_t best_of_cb = INT64_MAX;
     int tps_of_cb = 1;
     for (int per_cu = most; per_cu >= 1; --per_cu) {

@@ -288,3 +288,24 @@ def test_tile_widths_and_feature_quads(gg, basis, shape):
     _, s64 = g.fitness(torch.from_numpy(W).cuda(), with64=True)
     assert np.array_equal(s64.cpu().numpy(), f64)
     g.close()
+
+
+@pytest.mark.parametrize("basis", [0, 1, 2])
+@pytest.mark.parametrize("shape", [
+    # NP, N, d, P: one feature, an odd last one, whole groups, one less than the
+    # group in quads and singly, single rows past a tile, one and two column blocks
+    (1, 1, 1, 2), (257, 15, 1, 33), (9001, 16, 1, 23), (700, 12, 1, 64), (256, 8, 2, 32),
+    (2000, 7, 4, 50), (511, 8, 4, 31), (300, 5, 3, 65), (640, 4, 3, 40)],
+    ids=lambda s: "x".join(map(str, s)))
+def test_narrow_rows_have_the_bits_of_wide_ones(gg, basis, shape):
+    """Rows of one group of features against the same rows with 20 features
+    more whose genes are zero (too wide for the narrow loop): products with
+    zero add nothing, so every error function ends with the same bits."""
+    NP, N, d, P = shape
+    X, t, W = problem(NP, N, d, P, basis, seed=NP + N + d + P)
+    Xw = np.concatenate([X, np.random.default_rng(1).uniform(-1, 1, (NP, 20)).astype(np.float32)], 1)
+    Ww = np.concatenate([W, np.zeros((P, 20 * d), np.float32)], 1)
+    for err in range(4):
+        f32, f64 = gpu_fitness(gg, basis, d, X, t, W, err)
+        w32, w64 = gpu_fitness(gg, basis, d, Xw, t, Ww, err)
+        assert np.array_equal(f32, w32) and np.array_equal(f64, w64), err
