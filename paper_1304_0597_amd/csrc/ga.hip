@@ -501,7 +501,6 @@ constexpr int kCompactGenes = 4;     // genes per thread
 constexpr int kCompactPopulation = 512;
 constexpr int kCompactTotal = 16384; // genes in all: 64 KB of LDS, four workgroups
 constexpr int kCompactBlocks = 2;    // blocks of selection words per pair
-constexpr int kCompactDraws = (8 * kCompactBlocks - 2) / 2;  // largest tournament: 7
 
 __global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactArgs a) {
   const RankArgs& ra = a.rank;
@@ -527,7 +526,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactAr
   // Partials: groups of w = 2^x >= n_splits lanes take a chromosome each (lane
   // l: split l).  Beyond 64 splits reduce_few_kernel has run.
   const bool few = !a.reduced;
-  const int w = ra.n_splits <= 8 ? 8 : ra.n_splits <= 16 ? 16 : ra.n_splits <= 32 ? 32 : 64;
+  const int w = ra.n_splits <= 16 ? 16 : ra.n_splits <= 32 ? 32 : 64;
   const int per = kCompactThreads / w;                        // chromosomes per round
   const int sub = tid / w, l = tid & (w - 1);
   constexpr int kRounds = 4;
@@ -580,7 +579,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactAr
       for (int u = 0; u < kRounds; ++u) {
         if (i0 + u * per >= P) break;
         double s = part[u];
-        for (int o = w >> 1; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        for (int o = w >> 1; o > 8; o >>= 1) s += __shfl_xor(s, o);
+        s = row_add<1>(row_add<2>(row_add<4>(row_add<8>(s))));
         const int i = i0 + u * per + sub;
         if (l == 0 && i < P) put_error(i, error_from_sum(s, ra.NP, ra.error_fn));
       }
@@ -604,8 +604,8 @@ __global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactAr
   if (wave == kWaves - 1) {
     uint64_t best = ~0ull;
     for (int i = lane; i < P; i += 64) best = min(best, keys[i]);
-    for (int o = 32; o > 0; o >>= 1)
-      best = min(best, (uint64_t)__shfl_xor((unsigned long long)best, o));
+    best = min8(best);
+    best = rows_min(min(best, row_move<kRowMirror>(best)));
     const int b = (int)(uint32_t)best;
     const double err = e64[b];
     const bool stop = err <= target || gen >= max_gen;
@@ -639,36 +639,26 @@ __global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactAr
     }
     __syncthreads();
   }
-  if (tid < n_pairs) {
-    const int q = tid;
+  // 16 lanes a pair: of the first and the other 8, each takes a draw of one
+  // parent (a lane per pair that read its draws in turn took 0.7 us longer).
+  for (int i = tid; i < 16 * n_pairs; i += kCompactThreads) {
+    const int q = i >> 4, parent = (i >> 3) & 1, d = i & 7;
     const uint32_t* wq = reinterpret_cast<const uint32_t*>(words + q * a.blocks * 4);
     const int k = g.selection == 0 ? g.k : 1;
-    int4 c;
-    if (g.selection == 1) {
-      c.x = ranking_pick(order, P, wq[0]);
-      c.y = ranking_pick(order, P, wq[1]);
-    } else if (g.selection == 2) {
-      c.x = roulette_pick(cum, P, wq[0]);
-      c.y = roulette_pick(cum, P, wq[1]);
-    } else {
-      // Lowest (fitness, index) of each parent's draws: the smallest key, all
-      // keys read before the first comparison.
-      uint64_t key[2 * kCompactDraws];
-#pragma unroll
-      for (int d = 0; d < 2 * kCompactDraws; ++d)
-        key[d] = d < 2 * k ? keys[(int)(((uint64_t)wq[d] * (uint64_t)P) >> 32)] : ~0ull;
-      uint64_t b1 = ~0ull, b2 = ~0ull;
-#pragma unroll
-      for (int d = 0; d < 2 * kCompactDraws; ++d) {
-        if (d < k) b1 = min(b1, key[d]);
-        else b2 = min(b2, key[d]);
-      }
-      c.x = (int)(uint32_t)b1;
-      c.y = (int)(uint32_t)b2;
+    int* c = reinterpret_cast<int*>(pair + q);
+    const uint32_t coin = wq[2 * k + parent];
+    if (g.selection == 0) {
+      // Lowest (fitness, index) of the draws: the smallest key.
+      const uint32_t u = wq[parent * k + min(d, k - 1)];
+      const uint64_t key = min8(keys[(int)(((uint64_t)u * (uint64_t)P) >> 32)]);
+      if (d == 0) c[parent] = (int)(uint32_t)key;
+    } else if (d == 0) {
+      c[parent] = g.selection == 1 ? ranking_pick(order, P, wq[parent])
+                                   : roulette_pick(cum, P, wq[parent]);
     }
-    c.z = (uint64_t)wq[2 * k] < g.thr_cross ? 1 : 0;
-    c.w = 1 + (int)(((uint64_t)wq[2 * k + 1] * (uint64_t)(K - 1)) >> 32);
-    pair[q] = c;
+    if (d == 1)
+      c[2 + parent] = parent ? 1 + (int)(((uint64_t)coin * (uint64_t)(K - 1)) >> 32)
+                             : (uint64_t)coin < g.thr_cross;
   }
   __syncthreads();
   const int best_i = best_sh;

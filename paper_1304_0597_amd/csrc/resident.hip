@@ -100,55 +100,6 @@ __device__ __forceinline__ float unit_error(const f32x16 (&acc)[2], float R) {
   return s;
 }
 
-// The 64-bit value of another lane of the 16-lane row (DPP control CTRL).
-template <int CTRL>
-__device__ __forceinline__ uint64_t row_move(uint64_t v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xF, 0xF, true);
-  return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
-}
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kHalfMirror = 0x141, kRowMirror = 0x140;
-constexpr int kRowRor = 0x120;
-
-// s + the same of lane l ^ N, where lanes 2 N apart hold equal values (N = 8:
-// any): a rotation of the row by N.
-template <int N>
-__device__ __forceinline__ double row_add(double s) {
-  return s + __longlong_as_double((long long)row_move<kRowRor + N>((uint64_t)__double_as_longlong(s)));
-}
-
-// The 64-bit value's two copies of v with the 32-lane halves (16-lane rows of
-// each half) doubled.
-template <bool ROWS>
-__device__ __forceinline__ void spread(uint64_t v, uint64_t& first, uint64_t& second) {
-  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-  if constexpr (ROWS) {
-    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto u = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    first = ((uint64_t)u[0] << 32) | l[0];
-    second = ((uint64_t)u[1] << 32) | l[1];
-  } else {
-    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto u = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    first = ((uint64_t)u[0] << 32) | l[0];
-    second = ((uint64_t)u[1] << 32) | l[1];
-  }
-}
-// Smallest of the lanes l ^ 16, l ^ 32, l ^ 48 and l.
-__device__ __forceinline__ uint64_t rows_min(uint64_t v) {
-  uint64_t x, y;
-  spread<true>(v, x, y);
-  spread<false>(min(x, y), x, y);
-  return min(x, y);
-}
-
-// Smallest key of each group of 8 lanes.
-__device__ __forceinline__ uint64_t min8(uint64_t k) {
-  k = min(k, row_move<kQuadXor1>(k));
-  k = min(k, row_move<kQuadXor2>(k));
-  return min(k, row_move<kHalfMirror>(k));
-}
-
 __global__ __launch_bounds__(kResThreads) void resident_kernel(ResidentArgs a) {
   extern __shared__ double lds8[];
   const GAArgs& g = a.ga;
