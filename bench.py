@@ -609,8 +609,8 @@ def form_degree_sweep(gg, degrees=(1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16), reps=25)
     K - 1 = 32 d expansion terms): FP32 and BF16 kernel time (median of
     `reps` HIP-event-timed launches after 30 untimed ones) and fraction of
     each precision's MFMA peak.  Shows the tile choices the plans make: FP32
-    128-chromosome tiles while the genes fit one LDS chunk (d <= 8 here),
-    64-chromosome tiles through two gene buffers above; BF16 eight waves
+    128-chromosome tiles, their genes staged once while they fit one LDS chunk
+    (d <= 9 here) and through two gene buffers above; BF16 eight waves
     per workgroup where a lane half's group holds at most 4 sub-features,
     four waves otherwise."""
     import torch

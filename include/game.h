@@ -211,8 +211,10 @@ int game_step(game_t h);
  * maximum number of iterations of Sec. 5.  The loop is captured in a HIP
  * graph of 8 generations (no host round trip per generation); replays are
  * queued two at a time with two such chunks in flight, and queuing ends once
- * the device stop flag, copied back after each chunk, shows the run stopped
- * (chunks queued meanwhile do nothing).  With a surrogate attached the
+ * the device stop flag, written to the host after each chunk, shows the run
+ * stopped (chunks queued meanwhile do nothing).  The smallest float32 runs
+ * (at most 64 chromosomes, the expanded data set within one CU's LDS) go
+ * through up to 1,024 generations per launch of one workgroup instead.  With a surrogate attached the
  * generations are queued on the stream directly, 8 per chunk, with the same
  * stop checks (its few hundred short launches per generation run faster
  * that way).  Synchronises the stream.  max_generations < 0 and target < 0

@@ -53,9 +53,9 @@ inline int max_splits(int ld_partial) {
   return c > kMaxSplits ? c : kMaxSplits;
 }
 
-// Fitness tile geometry: a workgroup of 4 waves covers 256 patterns x 64
-// chromosomes; each wave 64 patterns (two 32-row MFMA blocks) x 64
-// chromosomes (two 32-column MFMA blocks).
+// Fitness tile geometry: a wave covers 64 patterns (two 32-row MFMA blocks) of
+// a 256-pattern tile x 32, 64 or 128 chromosomes (32-column MFMA blocks);
+// kTileCols is the width of a batch's items.
 constexpr int kTileRows = 256;
 constexpr int kTileCols = 64;
 constexpr int kFitThreads = 256;
@@ -69,7 +69,8 @@ constexpr int kMaxChunkSteps = 128;
 constexpr int kMaxWideSteps = 159;
 constexpr int kChunkSteps = 64;
 
-// Device-side state of a run.  Only the rank kernel writes gen/stop/best.
+// Device-side state of a run.  gen, stop and best are written by the launch that
+// ends a generation (finish_rank, the compact tail) or by the resident kernel.
 struct RunState {
   int32_t gen;          // index of the population to be evaluated next
   int32_t stop;         // 1 once a stop criterion held
@@ -129,7 +130,7 @@ struct FitArgs {
   int32_t degree;           // d
   int32_t basis;            // expansion family (the kernels take it as a template parameter)
   const float* cs;          // trig only: [NP x N] pairs (cos x, sin x) of X, or null
-  int32_t tile_cols;        // chromosomes per FP32 tile: 64, or 128 (genes in one chunk)
+  int32_t tile_cols;        // chromosomes per FP32 tile: 32, 64 or 128
   DrawArgs draw;            // float32 launches only
 };
 
@@ -137,9 +138,9 @@ struct FitArgs {
 // stored (cos x, sin x) table FitArgs::cs.
 constexpr int kTrigTable = 4;
 
-// Grid/chunk planning shared by every float32 fitness launch.  wide allows
-// 128-chromosome tiles (single runs); the batched kernel's items are 64
-// chromosomes wide.
+// Grid/chunk planning shared by every float32 fitness launch.  wide: 32, 64 or
+// 128 chromosomes to a tile, by estimated time (single runs); the batched
+// kernel's items are 64 chromosomes wide.
 void plan_fitness(FitArgs& a, int degree, int basis, bool wide);
 size_t fitness_lds_bytes(const FitArgs& a, int degree);
 
