@@ -25,12 +25,13 @@ __host__ __device__ constexpr int row_stride(int nf) { return nf | 1; }
 using ConstGene = __attribute__((address_space(4))) const float;
 
 // Copies features [f0, f0 + nf) of patterns [row0, row0 + n_rows) into LDS
-// rows of stride S, the workgroup reading consecutive addresses.  Element e
-// of the piece is row e / nf, column e % nf; a step of kRows elements
-// advances both without a division.
+// rows of stride S, the workgroup of THREADS reading consecutive addresses.
+// Element e of the piece is row e / nf, column e % nf; a step of THREADS
+// elements advances both without a division.
+template <int THREADS = kRows>
 __device__ __forceinline__ void stage_rows(float* rows, int S, const float* X, int64_t row0,
                                            int n_rows, int N, int f0, int nf) {
-  const int q = kRows / nf, rem = kRows - q * nf;
+  const int q = THREADS / nf, rem = THREADS - q * nf;
   int row = threadIdx.x / nf, col = threadIdx.x - row * nf;
   const float* src = X + row0 * N + f0;
   while (row < n_rows) {
