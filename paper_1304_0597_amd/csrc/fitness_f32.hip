@@ -54,9 +54,9 @@
 
 namespace game {
 
-// ROWS: the general tile body, or the one for narrow rows, single features or
-// whole quads at a time.
-enum { kGeneralRows, kNarrowRows, kNarrowQuads };
+// ROWS: the general tile body, the one for narrow rows, single features or
+// whole quads at a time, or the general one reading two quads at a time.
+enum { kGeneralRows, kNarrowRows, kNarrowQuads, kQuadRows };
 template <int BASIS, int D, int CB, int ROWS>
 __global__ __launch_bounds__(64 * fit_waves(CB), (ROWS && CB == 1 ? 16 : 8) / fit_waves(CB)) void
 fitness_f32_kernel(FitArgs a) {
@@ -84,6 +84,8 @@ fitness_f32_kernel(FitArgs a) {
   const int ctile = L - split * a.n_ctiles;
   if constexpr (ROWS == kGeneralRows)
     fitness_f32_block<BASIS, D, CB>(a, genes, split, ctile, lds, a.stop);
+  else if constexpr (ROWS == kQuadRows)
+    fitness_f32_block<BASIS, D, CB, 2, 4>(a, genes, split, ctile, lds, a.stop);
   else
     fitness_f32_narrow<BASIS, D, CB, ROWS == kNarrowQuads>(a, genes, split, ctile, lds, a.stop);
   if (b == 0 && threadIdx.x == 0) {
@@ -94,7 +96,9 @@ fitness_f32_kernel(FitArgs a) {
 
 template <int BASIS, int D, int CB, int ROWS>
 static hipError_t launch_rows(const FitArgs& a, hipStream_t s) {
-  const size_t lds = ROWS ? fit_waves(CB) * 32 * CB * sizeof(double) : fitness_lds_bytes(a, D);
+  const size_t lds = ROWS == kNarrowRows || ROWS == kNarrowQuads
+                         ? fit_waves(CB) * 32 * CB * sizeof(double)
+                         : fitness_lds_bytes(a, D);
   const int threads = 64 * fit_waves(CB);
   const int grid = a.n_ctiles * a.n_splits + (a.draw.n_items + threads - 1) / threads;
   if (lds > 65536) {
@@ -113,6 +117,12 @@ static hipError_t launch_cb(const FitArgs& a, hipStream_t s) {
       return a.N % 4 == 0 && reinterpret_cast<uintptr_t>(a.X) % 16 == 0
                  ? launch_rows<BASIS, D, CB, kNarrowQuads>(a, s)
                  : launch_rows<BASIS, D, CB, kNarrowRows>(a, s);
+  }
+  // Wide tiles of rows that are pairs of quads: 1,000,000 x 32, 2,048
+  // chromosomes, degree 1 1,266 us (1,416 by pairs), degree 2 2,151 (2,193).
+  if constexpr (BASIS < 3 && D <= 2 && CB == 4) {
+    if (a.N % 8 == 0 && reinterpret_cast<uintptr_t>(a.X) % 16 == 0)
+      return launch_rows<BASIS, D, CB, kQuadRows>(a, s);
   }
   return launch_rows<BASIS, D, CB, kGeneralRows>(a, s);
 }
@@ -206,14 +216,21 @@ void plan_fitness(FitArgs& a, int degree, int basis, bool wide) {
       splits = std::min({std::max(splits, 1), max_splits(ctiles * 32 * cb), a.n_tiles});
       const int tps = (a.n_tiles + splits - 1) / splits;
       const int64_t groups = (int64_t)ctiles * ((a.n_tiles + tps - 1) / tps);
-      const int64_t w = (groups + 255) / 256 * std::min(streams, tps);
-      const int64_t cost = w * ((tps + streams - 1) / streams) * step_cost(cb, a.Q * degree, (int)w);
+      // An odd tile count leaves one of a wide workgroup's streams its last tile
+      // alone.
+      const int64_t per_cu_groups = (groups + 255) / 256;
+      const int64_t w = per_cu_groups * std::min(streams, tps);
+      const int64_t cost = per_cu_groups * (streams == 1
+                               ? tps * step_cost(cb, a.Q * degree, (int)w)
+                               : (tps & ~1) * step_cost(cb, a.Q * degree, 2) +
+                                     (tps & 1) * step_cost(cb, a.Q * degree, 1));
       if (best_of_cb == INT64_MAX || cost + cost / 32 < best_of_cb) {
         best_of_cb = cost;
         tps_of_cb = tps;
       }
     }
-    if (best_of_cb < best) {
+    // (narrower tiles only where they win clearly: the estimate is within 15 %)
+    if (best == INT64_MAX || best_of_cb + best_of_cb / 8 < best) {
       best = best_of_cb;
       best_cb = cb;
       best_tps = tps_of_cb;

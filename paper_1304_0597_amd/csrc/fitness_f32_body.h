@@ -70,9 +70,11 @@ __device__ __forceinline__ void swap_halves(float a, float b, float& lo, float& 
 
 // Feature pairs whose loads are issued together, a group ahead of their use.
 // A pair of degree d is 2 d CB MFMAs of work; at low degree that is far less
-// than a load's latency.
+// than a load's latency.  Eight waves of wide tiles cover it with one pair at a
+// time (groups of 4 cost them 3-7 % where the last is not whole: 361,685 x 5,
+// Legendre 2, 920 chromosomes 117 us for 110); only whole quads pay (kQuadRows).
 __host__ __device__ constexpr int pairs_ahead(int d, int cb) {
-  return cb == 4 ? (d <= 2 ? 4 : d == 4 ? 2 : 1) : (d == 1 ? 8 : d <= 4 ? 4 : d <= 8 ? 2 : 1);
+  return cb == 4 ? 1 : (d == 1 ? 8 : d <= 4 ? 4 : d <= 8 ? 2 : 1);
 }
 
 // Tile range [split's tiles] x chromosome tile ctile (32*CB chromosomes,
@@ -81,9 +83,9 @@ __host__ __device__ constexpr int pairs_ahead(int d, int cb) {
 // (its 64-row slice of each: RB 32-row blocks).  genes: the chromosomes
 // being scored; lds: the workgroup's dynamic LDS; stop: when set and nonzero
 // nothing is computed.  D is the degree.  BASIS
-// is the expansion family (kTrigTable: the trigonometric one seeded from
+// is the expansion family, QP the feature pairs loaded at a time (kTrigTable: the trigonometric one seeded from
 // the stored (cos x, sin x) table a_in.cs instead of sincosf in every tile).
-template <int BASIS, int D, int CB = 2, int RB = 2>
+template <int BASIS, int D, int CB = 2, int RB = 2, int QP = RB == 2 ? pairs_ahead(D, CB) : 1>
 __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const float* __restrict__ genes,
                                                   int split, int ctile, float* lds,
                                                   const int32_t* stop = nullptr) {
@@ -126,7 +128,6 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
   constexpr int TPW = RB / 2;         // consecutive row tiles per wave
   constexpr int STEP = TS * TPW;      // row tiles per step of the workgroup
   constexpr int kCols = 32 * CB;      // chromosomes per tile
-  constexpr int QP = RB == 2 ? pairs_ahead(D, CB) : 1;   // feature pairs loaded at a time
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int wq = wave & 3;            // 64-row slice of a tile
