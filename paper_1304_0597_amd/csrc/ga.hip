@@ -498,9 +498,15 @@ hipError_t launch_ga_next(const GAArgs& a, hipStream_t s) {
 // launch recorded, so workgroup 0's update cannot be seen by another one.
 constexpr int kCompactThreads = 1024;
 constexpr int kCompactGenes = 4;     // genes per thread
+constexpr int kCompactRounds = 4;    // partials per thread
 constexpr int kCompactPopulation = 512;
 constexpr int kCompactTotal = 16384; // genes in all: 64 KB of LDS, four workgroups
 constexpr int kCompactBlocks = 2;    // blocks of selection words per pair
+
+// Lanes that take a chromosome's partials, one each.
+__host__ __device__ constexpr int split_lanes(int splits) {
+  return splits <= 16 ? 16 : splits <= 32 ? 32 : 64;
+}
 
 __global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactArgs a) {
   const RankArgs& ra = a.rank;
@@ -524,23 +530,21 @@ __global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactAr
   const double target = st->target;
   const int n = P * K, first = blockIdx.x * kCompactThreads * kCompactGenes;
   // Partials: groups of w = 2^x >= n_splits lanes take a chromosome each (lane
-  // l: split l).  Beyond 64 splits reduce_few_kernel has run.
+  // l: split l), or reduce_few_kernel has run.
   const bool few = !a.reduced;
-  const int w = ra.n_splits <= 16 ? 16 : ra.n_splits <= 32 ? 32 : 64;
+  const int w = split_lanes(ra.n_splits);
   const int per = kCompactThreads / w;                        // chromosomes per round
   const int sub = tid / w, l = tid & (w - 1);
-  constexpr int kRounds = 4;
-  double part[kRounds];
-  auto load_partials = [&](int i0) {
+  double part[kCompactRounds];
+  if (few) {
 #pragma unroll
-    for (int u = 0; u < kRounds; ++u) {
-      const int i = i0 + u * per + sub;
+    for (int u = 0; u < kCompactRounds; ++u) {
+      const int i = u * per + sub;
       const bool ok = i < P && l < ra.n_splits;
       const double p = ra.partial[ok ? (int64_t)l * ra.ld_partial + i : 0];
       part[u] = ok ? 0.0 + p : 0.0;
     }
-  };
-  if (few) load_partials(0);
+  }
   constexpr int kPop = 4;
   float v[kPop];
   auto load_pop = [&](int i0) {
@@ -573,17 +577,14 @@ __global__ __launch_bounds__(kCompactThreads) void compact_tail_kernel(CompactAr
     }
   };
   if (few) {
-    for (int i0 = 0; i0 < P; i0 += per * kRounds) {
-      if (i0) load_partials(i0);
 #pragma unroll
-      for (int u = 0; u < kRounds; ++u) {
-        if (i0 + u * per >= P) break;
-        double s = part[u];
-        for (int o = w >> 1; o > 8; o >>= 1) s += __shfl_xor(s, o);
-        s = row_add<1>(row_add<2>(row_add<4>(row_add<8>(s))));
-        const int i = i0 + u * per + sub;
-        if (l == 0 && i < P) put_error(i, error_from_sum(s, ra.NP, ra.error_fn));
-      }
+    for (int u = 0; u < kCompactRounds; ++u) {
+      if (u * per >= P) break;
+      double s = part[u];
+      for (int o = w >> 1; o > 8; o >>= 1) s += __shfl_xor(s, o);
+      s = row_add<1>(row_add<2>(row_add<4>(row_add<8>(s))));
+      const int i = u * per + sub;
+      if (l == 0 && i < P) put_error(i, error_from_sum(s, ra.NP, ra.error_fn));
     }
   } else {
     for (int i = tid; i < P; i += kCompactThreads) put_error(i, ra.fit64[i]);
@@ -705,7 +706,12 @@ bool compact_fits(int P, int K, int k, int selection) {
 
 hipError_t launch_compact_tail(CompactArgs a, hipStream_t s) {
   const GAArgs& g = a.ga;
-  a.reduced = a.rank.n_splits > 64;
+  // Partials beyond a few rounds of one workgroup are summed by a launch of their
+  // own over all CUs: a generation of 12,000 patterns, 400 chromosomes and 47 splits
+  // took 34 us without it and takes 15, 4,000 and
+  // 511 with 16 splits 16.5 and 14.
+  const int splits = a.rank.n_splits;
+  a.reduced = splits > 64 || g.P * split_lanes(splits) > kCompactRounds * kCompactThreads;
   if (a.reduced) {
     const hipError_t e = launch_reduce_few(a.rank, s);
     if (e != hipSuccess) return e;
