@@ -72,9 +72,11 @@ __device__ __forceinline__ void swap_halves(float a, float b, float& lo, float& 
 // A pair of degree d is 2 d CB MFMAs of work; at low degree that is far less
 // than a load's latency.  Eight waves of wide tiles cover it with one pair at a
 // time (groups of 4 cost them 3-7 % where the last is not whole: 361,685 x 5,
-// Legendre 2, 920 chromosomes 117 us for 110); only whole quads pay (kQuadRows).
+// Legendre 2, 920 chromosomes 117 us for 110); only whole quads pay (kQuadRows),
+// and two pairs at degree 4 (200,000 x 20, trigonometric, 2,048 chromosomes 992 us
+// for 1,018).
 __host__ __device__ constexpr int pairs_ahead(int d, int cb) {
-  return cb == 4 ? 1 : (d == 1 ? 8 : d <= 4 ? 4 : d <= 8 ? 2 : 1);
+  return cb == 4 ? (d == 4 ? 2 : 1) : (d == 1 ? 8 : d <= 4 ? 4 : d <= 8 ? 2 : 1);
 }
 
 // Tile range [split's tiles] x chromosome tile ctile (32*CB chromosomes,
