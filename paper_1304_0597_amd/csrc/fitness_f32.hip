@@ -176,9 +176,12 @@ static int max_staged_steps(int cb) { return cb == 4 ? kMaxWideSteps : kMaxChunk
 // LDS in chunks cost the more the narrower the tile.  Fitted to launches of 16
 // to 320 expansion terms and 23 to 2,048 chromosomes (within 5 % of their
 // times, for 64-chromosome tiles within 15).
-static int64_t step_cost(int cb, int ksteps, int w) {
+static int64_t step_cost(int cb, int pairs, int degree, int w) {
+  const int ksteps = pairs * degree;
   const int64_t m = 128 * cb * (ksteps + 1);
-  int64_t v = cb == 4 ? 4200 + 40 * ksteps : cb == 2 ? 3400 + 40 * ksteps : 1800 + 17 * ksteps;
+  // per feature pair (its loads, its seed) and per degree
+  int64_t v = cb == 1 ? 1800 + 60 * pairs + 9 * ksteps
+                      : (cb == 4 ? 4200 : 3400) + 100 * pairs + 27 * ksteps;
   if (ksteps > max_staged_steps(cb)) v += m * (cb == 4 ? 13 : cb == 2 ? 40 : 55) / 100;
   return m + (w > 1 ? v : 2 * v);
 }
@@ -211,6 +214,7 @@ void plan_fitness(FitArgs& a, int degree, int basis, bool wide) {
     const int most = cb == 4 ? 1 : cb == 2 ? 2 : a.Q * degree <= 16 && !narrow ? 8 : 4;
     int64_t best_of_cb = INT64_MAX;
     int tps_of_cb = 1;
+    int64_t start_of_cb = 0;       // start-up of a CU's workgroups
     for (int per_cu = most; per_cu >= 1; --per_cu) {
       int splits = 256 * per_cu / ctiles;
       splits = std::min({std::max(splits, 1), max_splits(ctiles * 32 * cb), a.n_tiles});
@@ -221,14 +225,16 @@ void plan_fitness(FitArgs& a, int degree, int basis, bool wide) {
       const int64_t per_cu_groups = (groups + 255) / 256;
       const int64_t w = per_cu_groups * std::min(streams, tps);
       const int64_t cost = per_cu_groups * (streams == 1
-                               ? tps * step_cost(cb, a.Q * degree, (int)w)
-                               : (tps & ~1) * step_cost(cb, a.Q * degree, 2) +
-                                     (tps & 1) * step_cost(cb, a.Q * degree, 1));
+                               ? tps * step_cost(cb, a.Q, degree, (int)w)
+                               : (tps & ~1) * step_cost(cb, a.Q, degree, 2) +
+                                     (tps & 1) * step_cost(cb, a.Q, degree, 1));
       if (best_of_cb == INT64_MAX || cost + cost / 32 < best_of_cb) {
         best_of_cb = cost;
         tps_of_cb = tps;
+        start_of_cb = per_cu_groups * 1500;
       }
     }
+    best_of_cb += start_of_cb;
     // (narrower tiles only where they win clearly: the estimate is within 15 %)
     if (best == INT64_MAX || best_of_cb + best_of_cb / 8 < best) {
       best = best_of_cb;
