@@ -267,10 +267,11 @@ def test_trig_table_gives_the_kernels_own_bits(gg, shape):
 @pytest.mark.parametrize("shape", [
     # NP, N, d, P: 32-, 64- and 128-chromosome tiles; feature quads whole and
     # with a half-filled last group, rows that are no whole quads; genes in
-    # chunks under narrow tiles, of whole quads and not
+    # chunks under narrow tiles, of whole quads and not; wide tiles of rows that
+    # are pairs of quads
     (7001, 16, 1, 23), (7001, 12, 2, 40), (5000, 20, 3, 33), (5000, 24, 4, 65), (3000, 6, 4, 20),
     (2000, 40, 8, 30), (2000, 300, 2, 20), (1000, 120, 3, 30), (60000, 8, 2, 64),
-    (300, 4, 1, 1500)], ids=lambda s: "x".join(map(str, s)))
+    (300, 4, 1, 1500), (9001, 24, 1, 3000), (20001, 40, 2, 900)], ids=lambda s: "x".join(map(str, s)))
 def test_tile_widths_and_feature_quads(gg, basis, shape):
     """Errors against the oracle, and the same bits from an X that starts 4
     bytes past a 16-byte boundary (features then read one by one)."""
