@@ -177,8 +177,12 @@ hipError_t launch_variant(PredictArgs a, hipStream_t s) {
       STAGE ? (size_t)kRows * row_stride(std::min(a.N, kChunk)) * sizeof(float) : 0;
   if (!a.counts) {
     // Once the pattern tiles alone fill the GPU a workgroup serves several
-    // chromosome groups in turn with one read of its rows.
-    const int64_t gx = std::min<int64_t>(tiles, 1 << 24);
+    // chromosome groups in turn with one read of its rows.  A launch dimension
+    // holds less than 2^32 threads: beyond 2^28 patterns a workgroup takes
+    // several tiles.
+    constexpr int64_t kMostTiles = 1 << 20;
+    static_assert(kMostTiles * kRows < (int64_t)1 << 32, "threads of a launch dimension");
+    const int64_t gx = std::min(tiles, kMostTiles);
     const int64_t gy = std::min(groups, std::max<int64_t>(1, 2048 / gx));
     hipLaunchKernelGGL((predict_kernel<BASIS, D, R, STAGE>), dim3((unsigned)gx, (unsigned)gy),
                        dim3(kRows), lds, s, a);

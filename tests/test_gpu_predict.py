@@ -148,3 +148,21 @@ def test_outputs_and_counts_at_tile_edges(gg, basis, d, NP, N, n):
         counts = g.classify(gd, threshold=0.1).cpu().numpy()
         assert np.array_equal(counts, _counts_from(out, t, 0.1))
     g.close()
+
+
+def test_predict_beyond_2_to_the_32_patterns(gg):
+    """More patterns than a launch dimension has threads: a workgroup takes
+    several tiles.  Small whole features and genes, so every output is exact;
+    the last patterns lie past 2^32, the last tile is ragged."""
+    NP, step = (1 << 32) + 333, 1 << 28
+    X = torch.empty((NP, 1), dtype=torch.float32, device="cuda")
+    for r in range(0, NP, step):
+        n = min(step, NP - r)
+        X[r:r + n, 0] = (torch.arange(r, r + n, device="cuda") % 251).float()
+    cfg = gg.config(basis=2, degree=1, population=2, tournament_k=1, elitism=1)
+    g = gg.Game(cfg, X[:100], torch.zeros(100, device="cuda"))
+    out = g.predict(torch.tensor([[0.5, 2.0]], device="cuda"), X)
+    for r in range(0, NP, step):
+        n = min(step, NP - r)
+        assert torch.equal(out[0, r:r + n], X[r:r + n, 0] * 2 + 0.5), r
+    g.close()
