@@ -6,6 +6,7 @@ a relative bound with an absolute floor for fitness values near zero.
 import numpy as np
 import pytest
 
+from fitness_plan import plan
 from oracle import game as og
 from paper_1304_0597_amd import datagen
 
@@ -310,3 +311,14 @@ def test_narrow_rows_have_the_bits_of_wide_ones(gg, basis, shape):
         f32, f64 = gpu_fitness(gg, basis, d, X, t, W, err)
         w32, w64 = gpu_fitness(gg, basis, d, Xw, t, Ww, err)
         assert np.array_equal(f32, w32) and np.array_equal(f64, w64), err
+
+
+@pytest.mark.parametrize("splits", [1, 64, 65, 128, 129, 256, 257, 600])
+def test_split_sums_at_the_ends_of_their_rounds(gg, splits):
+    """The partials of 64 splits are a round of a wave; one, two, four and
+    eight rounds' loads go out together."""
+    NP = 256 * splits - 3
+    assert plan(NP, 9, 2, 5).splits == splits
+    X, t, W = problem(NP, 9, 2, 5, 0, seed=splits)
+    _, f64 = gpu_fitness(gg, 0, 2, X, t, W)
+    assert within(f64, og.fitness(X, t, W, 0, 2), t).all()
