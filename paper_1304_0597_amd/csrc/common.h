@@ -278,7 +278,11 @@ struct CompactArgs {
   int32_t need_order;       // set by the launch
   int32_t pair_at;          // set by the launch
 };
-bool compact_fits(int P, int K, int k, int selection);
+// Whether the genetic step reads the whole rank order, not the best alone.
+inline bool reads_order(const GAArgs& g) {
+  return g.selection == 1 || (g.elite_mode == 1 && g.E > 0);
+}
+bool compact_fits(const GAArgs& g);
 int compact_blocks(int k, int selection);
 hipError_t launch_compact_tail(CompactArgs a, hipStream_t s);
 // Up to `generations` generations of a run in one launch (see resident.hip),

@@ -500,6 +500,7 @@ constexpr int kCompactThreads = 1024;
 constexpr int kCompactGenes = 4;     // genes per thread
 constexpr int kCompactRounds = 4;    // partials per thread
 constexpr int kCompactPopulation = 512;
+constexpr int kCompactOrdered = 192; // chromosomes, where their rank order is read
 constexpr int kCompactTotal = 16384; // genes in all: 64 KB of LDS, four workgroups
 constexpr int kCompactBlocks = 2;    // blocks of selection words per pair
 
@@ -698,10 +699,15 @@ static size_t compact_lds(int P, int K, int E, int blocks, int* pair_at) {
 int compact_blocks(int k, int selection) { return (2 * (selection == 0 ? k : 1) + 2 + 7) / 8; }
 
 // Runs whose tail takes one launch; larger populations keep the separate
-// launches, which spread over more CUs.
-bool compact_fits(int P, int K, int k, int selection) {
-  return P <= kCompactPopulation && (int64_t)P * K <= kCompactTotal &&
-         compact_blocks(k, selection) <= kCompactBlocks;
+// launches, which spread over more CUs.  So do those whose rank order is read, from
+// a smaller size on: every workgroup counts the P x P comparisons for itself.
+// Ranking selection, a generation in one launch and the fitness launch, and in
+// separate ones: 128 chromosomes of 121 genes 21.6 and 23.1 us, 200 of 81 22.3 and
+// 21.6, 256 of 64 24.1 and 20.0, 511 of 32 31.2 and 22.2 (without the order 19.9
+// and 22.1).
+bool compact_fits(const GAArgs& g) {
+  return g.P <= (reads_order(g) ? kCompactOrdered : kCompactPopulation) &&
+         (int64_t)g.P * g.K <= kCompactTotal && compact_blocks(g.k, g.selection) <= kCompactBlocks;
 }
 
 hipError_t launch_compact_tail(CompactArgs a, hipStream_t s) {
@@ -716,7 +722,7 @@ hipError_t launch_compact_tail(CompactArgs a, hipStream_t s) {
     const hipError_t e = launch_reduce_few(a.rank, s);
     if (e != hipSuccess) return e;
   }
-  a.need_order = g.selection == 1 || (g.elite_mode == 1 && g.E > 0);
+  a.need_order = reads_order(g);
   const size_t lds = compact_lds(g.P, g.K, g.E, a.blocks, &a.pair_at);
   if (lds > 48 * 1024) {
     const hipError_t e = hipFuncSetAttribute((const void*)compact_tail_kernel,

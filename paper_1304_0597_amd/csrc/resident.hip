@@ -398,7 +398,7 @@ constexpr size_t kResLds = 159 * 1024;
 static bool resident_args(const FitArgs& f, const GAArgs& g, ResidentArgs& a) {
   const int64_t units = (f.NP + 63) / 64, S = (int64_t)f.Q * f.degree;
   const int blocks = compact_blocks(g.k, g.selection);
-  if (!compact_fits(g.P, g.K, g.k, g.selection) || g.P > kResPopulation ||
+  if (!compact_fits(g) || g.P > kResPopulation ||
       f.tiles_per_split != 1 || f.n_tiles > 32 || (f.basis == 3 && !f.cs))
     return false;
   const int nct = (g.P + 31) / 32;
@@ -426,7 +426,7 @@ static bool resident_args(const FitArgs& f, const GAArgs& g, ResidentArgs& a) {
   a.error_fn = f.error_fn;
   a.R = f.R;
   a.blocks = blocks;
-  a.need_order = g.selection == 1 || (g.elite_mode == 1 && g.E > 0);
+  a.need_order = reads_order(g);
   a.ga = g;
   return resident_layout(a) <= kResLds;
 }

@@ -103,10 +103,26 @@ bool keeps_trig_table(const game_config* c) {
 // Classification sums; zeroed at create, and every launch leaves them zero.
 constexpr size_t kTallyBytes = kTallyChromosomes * 4 * sizeof(int64_t);
 
+uint64_t coin_threshold(float p) { return (uint64_t)floor((double)p * 4294967296.0); }
+
+GAArgs ga_args(const game_config* c, int32_t K) {
+  GAArgs g{};
+  g.P = c->population;
+  g.K = K;
+  g.k = c->tournament_k;
+  g.E = c->elitism;
+  g.elite_mode = c->elite_mode;
+  g.thr_cross = coin_threshold(c->p_crossover);
+  g.thr_mut = coin_threshold(c->p_mutation);
+  g.sigma = c->sigma_mutation;
+  g.seed = c->seed;
+  g.selection = c->selection;
+  return g;
+}
+
 // Float32 runs whose generation tail is one launch (compact_fits).
 bool compact_run(const game_config* c, int32_t K) {
-  return c->precision == GAME_FP32 &&
-         compact_fits(c->population, K, c->tournament_k, c->selection);
+  return c->precision == GAME_FP32 && compact_fits(ga_args(c, K));
 }
 
 Layout layout(const game_config* c, int64_t n_patterns, int32_t n_features) {
@@ -138,8 +154,6 @@ Layout layout(const game_config* c, int64_t n_patterns, int32_t n_features) {
   L.total = off;
   return L;
 }
-
-uint64_t coin_threshold(float p) { return (uint64_t)floor((double)p * 4294967296.0); }
 
 }  // namespace
 
@@ -253,21 +267,6 @@ hipError_t rescore64(const game_ctx* h, const float* X, const float* t, int64_t 
   r.error_fn = h->cfg.error_fn;
   r.R = h->cfg.tmse_R;
   return launch_rescore64(r, h->cfg.basis, h->cfg.degree, out, s);
-}
-
-GAArgs ga_args(const game_config* c, int32_t K) {
-  GAArgs g{};
-  g.P = c->population;
-  g.K = K;
-  g.k = c->tournament_k;
-  g.E = c->elitism;
-  g.elite_mode = c->elite_mode;
-  g.thr_cross = coin_threshold(c->p_crossover);
-  g.thr_mut = coin_threshold(c->p_mutation);
-  g.sigma = c->sigma_mutation;
-  g.seed = c->seed;
-  g.selection = c->selection;
-  return g;
 }
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }

@@ -416,3 +416,15 @@ def test_whole_runs_equal_their_generations(gg, case):
     a.close()
     b.close()
     e.close()
+
+
+@pytest.mark.parametrize("case", [
+    # the largest population whose rank order is made inside the one-launch tail,
+    # and one past it: ranking selection, the best kept, and both
+    (700, 20, 4, 192, dict(selection=1)), (700, 20, 4, 193, dict(selection=1)),
+    (700, 20, 4, 192, dict(elite_mode=1, elitism=3)), (700, 20, 4, 193, dict(elite_mode=1, elitism=3)),
+    (700, 20, 4, 192, dict(selection=1, elite_mode=1, elitism=2)),
+    (700, 20, 4, 193, dict(elite_mode=1, elitism=0))],
+    ids=lambda c: f"{c[0]}x{c[1]}-d{c[2]}-P{c[3]}-" + "-".join(f"{k}{v}" for k, v in c[4].items()))
+def test_generation_tail_with_its_rank_order(gg, case):
+    test_generation_tail_at_its_edges(gg, case)
