@@ -176,11 +176,13 @@ static int max_staged_steps(int cb) { return cb == 4 ? kMaxWideSteps : kMaxChunk
 // LDS in chunks cost the more the narrower the tile.  Fitted to launches of 16
 // to 320 expansion terms and 23 to 2,048 chromosomes (within 5 % of their
 // times, for 64-chromosome tiles within 15).
-static int64_t step_cost(int cb, int pairs, int degree, int w) {
+static int64_t step_cost(int cb, int pairs, int degree, int w, bool trig) {
   const int ksteps = pairs * degree;
   const int64_t m = 128 * cb * (ksteps + 1);
-  // per feature pair (its loads, its seed) and per degree
-  int64_t v = cb == 1 ? 1800 + 60 * pairs + 9 * ksteps
+  // per feature pair (its loads, its seed) and per degree.  Two MFMAs (degree 1 of
+  // a narrow tile) do not cover the reads of a pair of (cos x, sin x): 6,199 x 28,
+  // 777 chromosomes 19.5 us in 32s, which were taken at 60 a pair, 18.2 in 128s.
+  int64_t v = cb == 1 ? 1800 + (trig && degree == 1 ? 120 : 60) * pairs + 9 * ksteps
                       : (cb == 4 ? 4200 : 3400) + 100 * pairs + 27 * ksteps;
   if (ksteps > max_staged_steps(cb)) v += m * (cb == 4 ? 13 : cb == 2 ? 40 : 55) / 100;
   return m + (w > 1 ? v : 2 * v);
@@ -225,9 +227,9 @@ void plan_fitness(FitArgs& a, int degree, int basis, bool wide) {
       const int64_t per_cu_groups = (groups + 255) / 256;
       const int64_t w = per_cu_groups * std::min(streams, tps);
       const int64_t cost = per_cu_groups * (streams == 1
-                               ? tps * step_cost(cb, a.Q, degree, (int)w)
-                               : (tps & ~1) * step_cost(cb, a.Q, degree, 2) +
-                                     (tps & 1) * step_cost(cb, a.Q, degree, 1));
+                               ? tps * step_cost(cb, a.Q, degree, (int)w, basis == 3)
+                               : (tps & ~1) * step_cost(cb, a.Q, degree, 2, basis == 3) +
+                                     (tps & 1) * step_cost(cb, a.Q, degree, 1, basis == 3));
       if (best_of_cb == INT64_MAX || cost + cost / 32 < best_of_cb) {
         best_of_cb = cost;
         tps_of_cb = tps;
