@@ -139,6 +139,54 @@ __global__ __launch_bounds__(kRows / T) void rescore64_kernel(Rescore64Args a) {
     a.partial[(int64_t)blockIdx.x * a.n + c0 + threadIdx.x] = red[threadIdx.x][0];
 }
 
+// Fewer workgroups than CUs and many genes per feature (many_genes): block b takes
+// the tiles b, b + blocks, ... of one chromosome, its genes widened once into LDS.
+// The kernel above keeps 64 SGPRs of genes in flight, which is less the fewer
+// features that is, and nothing else on the CU covers the rest.
+template <int BASIS, int D>
+__global__ __launch_bounds__(kRows) void rescore64_few_kernel(Rescore64Args a) {
+  extern __shared__ double genes[];
+  __shared__ double red[kRows];
+  const int c = blockIdx.y;
+  const float* g = a.genes + (int64_t)c * a.K;
+  for (int i = threadIdx.x; i < a.K; i += blockDim.x) genes[i] = (double)g[i];
+  __syncthreads();
+  constexpr int B = BASIS == 3 ? 2 : 1;
+  double acc = 0.0;
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < a.NP;
+       k += (int64_t)gridDim.x * blockDim.x) {
+    double out = genes[0];
+    for (int f = 0; f < a.N; ++f) {
+      const double x = (double)a.X[k * a.N + f];
+      for (int b = 0; b < B; ++b) {
+        Recur<BASIS, double> rc;
+        rc.seed(x, b);
+        const double* w = genes + 1 + (f * B + b) * D;
+        auto term = [&](auto jc) {
+          constexpr int j = decltype(jc)::value;
+          out = fma(w[j], rc.cur, out);
+          if constexpr (j + 1 < D) rc.template advance<j + 1>(x);
+        };
+        [&]<int... J>(std::integer_sequence<int, J...>) {
+          (term(std::integral_constant<int, J>{}), ...);
+        }(std::make_integer_sequence<int, D>{});
+      }
+    }
+    const double r = (double)a.t[k] - out;
+    double e = r * r;
+    if (a.error_fn == 2) e = fabs(r) > a.R ? e : 0.0;
+    else if (a.error_fn == 3) e = e > a.R ? e : 0.0;
+    acc += e;
+  }
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int s = kRows / 2; s > 0; s >>= 1) {
+    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) a.partial[(int64_t)blockIdx.x * a.n + c] = red[0];
+}
+
 // Sum of each chromosome's block partials, one wave per chromosome: lane l
 // adds blocks l, l + 64, ... (at most 16 of them, all loaded before the first
 // addition), then a butterfly.  One thread adding 256 partials in turn took
@@ -158,6 +206,29 @@ __global__ __launch_bounds__(64) void rescore64_finish(const double* partial, in
   if (threadIdx.x == 0) out[c] = error_from_sum(s, NP, error_fn);
 }
 
+// The same for up to kFewBlocks blocks, a thread per chromosome: no workgroup for
+// each (255 x 7, Chebyshev 4, 16 chromosomes 5.3 us, 4.8 so).
+constexpr int kFewBlocks = 4;
+__global__ __launch_bounds__(256) void rescore64_finish_few(const double* partial, int32_t blocks,
+                                                            int32_t n, int64_t NP,
+                                                            int32_t error_fn, double* out) {
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= n) return;
+  double s = 0.0;
+  for (int b = 0; b < blocks; ++b) s += partial[(int64_t)b * n + c];
+  out[c] = error_from_sum(s, NP, error_fn);
+}
+
+// Where the genes of an unstaged launch go through LDS: by what a term computes to
+// cover its gene's load (a power least; sine and cosine have two genes a degree).
+// 1,000 patterns, one to three chromosomes, LDS and scalar loads: trigonometric 16 x
+// 8 features 9.0 and 10.0 us, 10 x 16 12.2 and 12.9, 4 x 30 17.0 and 16.8, 2 x 8 7.4
+// and 6.7; power 12 x 17 and Legendre 16 x 20 lose 7 to 11 % to scalar loads, Chebyshev
+// 10 x 32 and Legendre 8 x 32 gain 8 to 12.
+constexpr bool many_genes(int basis, int d) {
+  return d >= (basis == 3 ? 5 : basis == 2 ? 9 : 11);
+}
+
 template <int BASIS, int D, int R, int T, bool STAGE>
 static hipError_t launch_group(const Rescore64Args& a, hipStream_t s) {
   const size_t lds =
@@ -168,7 +239,8 @@ static hipError_t launch_group(const Rescore64Args& a, hipStream_t s) {
 }
 
 // Chromosomes per thread: one when groups of 4 would leave most CUs without
-// a workgroup, otherwise 1, 2 or 4 by their number.  Patterns per thread: two for
+// a workgroup (their genes through LDS where many_genes says so), otherwise 1, 2
+// or 4 by their number.  Patterns per thread: two for
 // sine and cosine, whose long serial evaluations then overlap (200,000 x 13: degree
 // 8, one chromosome 19.8 us, 26.5 with one; degree 3, five 31.4 and 43.5; four
 // patterns 23.5 and 32.8); one otherwise, where the waves lost cost more than the
@@ -176,8 +248,15 @@ static hipError_t launch_group(const Rescore64Args& a, hipStream_t s) {
 template <int BASIS, int D>
 static hipError_t launch_one(const Rescore64Args& a, hipStream_t s) {
   constexpr int T = BASIS == 3 ? 2 : 1;
-  if (!stages_rows((int64_t)a.blocks * ((a.n + 3) / 4)))
-    return launch_group<BASIS, D, 1, 1, false>(a, s);
+  if (!stages_rows((int64_t)a.blocks * ((a.n + 3) / 4))) {
+    if constexpr (many_genes(BASIS, D)) {
+      hipLaunchKernelGGL((rescore64_few_kernel<BASIS, D>), dim3(a.blocks, a.n), dim3(kRows),
+                         (size_t)a.K * sizeof(double), s, a);
+      return hipGetLastError();
+    } else {
+      return launch_group<BASIS, D, 1, 1, false>(a, s);
+    }
+  }
   if (a.n == 1) return launch_group<BASIS, D, 1, T, true>(a, s);
   return a.n == 2 ? launch_group<BASIS, D, 2, T, true>(a, s)
                   : launch_group<BASIS, D, 4, T, true>(a, s);
@@ -212,6 +291,11 @@ hipError_t launch_rescore64(const Rescore64Args& a, int basis, int degree, doubl
     return hipGetLastError();
   };
   static_assert(kRescoreBlocks == 64 * 16, "the widest finish");
+  if (a.blocks <= kFewBlocks) {
+    hipLaunchKernelGGL(rescore64_finish_few, dim3((a.n + 255) / 256), dim3(256), 0, s, a.partial,
+                       a.blocks, a.n, a.NP, a.error_fn, out);
+    return hipGetLastError();
+  }
   if (a.blocks <= 64) return finish(rescore64_finish<1>);
   if (a.blocks <= 256) return finish(rescore64_finish<4>);
   return finish(rescore64_finish<16>);

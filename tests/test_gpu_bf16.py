@@ -178,3 +178,19 @@ def test_rescore64_at_tile_edges(gg, basis, d, NP, N, n):
     ref = og.fitness(X, t, W[:n], basis, d)
     g.close()
     assert np.all(np.abs(got - ref) <= 1e-11 * ref)
+
+
+@pytest.mark.parametrize("basis,d", [(0, 10), (0, 11), (1, 10), (1, 16), (2, 8), (2, 9), (3, 4),
+                                     (3, 5), (3, 16)])
+@pytest.mark.parametrize("NP,N,n", [(255, 3, 17), (1024, 9, 2), (1025, 9, 1), (4097, 5, 3),
+                                    (30011, 3, 4)])
+def test_rescore64_of_few_patterns(gg, basis, d, NP, N, n):
+    """Fewer workgroups than CUs: genes by scalar loads and through LDS, on both
+    sides of that rule, one to 118 blocks, finished by threads and by waves."""
+    X, t, W = problem(NP, N, d, n, basis, seed=NP + d)
+    for error_fn in (0, 1):
+        g = make_game(gg, X, t, basis, d, max(n, 2), precision=0, error_fn=error_fn)
+        got = g.rescore64(torch.from_numpy(W).cuda()).cpu().numpy()
+        ref = og.fitness(X, t, W, basis, d, (og.MSE, og.RMSE)[error_fn])
+        g.close()
+        assert np.all(np.abs(got - ref) <= 1e-11 * ref)
