@@ -73,10 +73,12 @@ __device__ __forceinline__ void swap_halves(float a, float b, float& lo, float& 
 // than a load's latency.  Eight waves of wide tiles cover it with one pair at a
 // time (groups of 4 cost them 3-7 % where the last is not whole: 361,685 x 5,
 // Legendre 2, 920 chromosomes 117 us for 110); only whole quads pay (kQuadRows),
-// and two pairs at degree 4 (200,000 x 20, trigonometric, 2,048 chromosomes 992 us
-// for 1,018).
-__host__ __device__ constexpr int pairs_ahead(int d, int cb) {
-  return cb == 4 ? (d == 4 ? 2 : 1) : (d == 1 ? 8 : d <= 4 ? 4 : d <= 8 ? 2 : 1);
+// and two pairs of the trigonometric expansion at degree 4, whose (cos x, sin x)
+// are twice the bytes (six shapes 0.6 to 2.4 % faster, 200,000 x 20 with 2,048
+// chromosomes 996 us for 1,020; the polynomial bases on the same shapes from 1.8 %
+// slower to 1.1 % faster, and at degrees 1 to 3 two pairs cost up to 2.8 %).
+__host__ __device__ constexpr int pairs_ahead(int d, int cb, bool trig = false) {
+  return cb == 4 ? (trig && d == 4 ? 2 : 1) : (d == 1 ? 8 : d <= 4 ? 4 : d <= 8 ? 2 : 1);
 }
 
 // Tile range [split's tiles] x chromosome tile ctile (32*CB chromosomes,
@@ -87,7 +89,8 @@ __host__ __device__ constexpr int pairs_ahead(int d, int cb) {
 // nothing is computed.  D is the degree.  BASIS
 // is the expansion family, QP the feature pairs loaded at a time (kTrigTable: the trigonometric one seeded from
 // the stored (cos x, sin x) table a_in.cs instead of sincosf in every tile).
-template <int BASIS, int D, int CB = 2, int RB = 2, int QP = RB == 2 ? pairs_ahead(D, CB) : 1>
+template <int BASIS, int D, int CB = 2, int RB = 2,
+          int QP = RB == 2 ? pairs_ahead(D, CB, BASIS >= 3) : 1>
 __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const float* __restrict__ genes,
                                                   int split, int ctile, float* lds,
                                                   const int32_t* stop = nullptr) {
