@@ -160,6 +160,8 @@ constexpr int kTrigTable = 4;
 // kernel's items are 64 chromosomes wide.
 void plan_fitness(FitArgs& a, int degree, int basis, bool wide);
 size_t fitness_lds_bytes(const FitArgs& a, int degree);
+// Whether a planned float32 launch takes the loop for narrow rows.
+bool narrow_rows(const FitArgs& a);
 
 hipError_t launch_fitness_f32(const FitArgs& a, int basis, int degree, hipStream_t s);
 // BF16 operands, FP32 accumulation: 128-chromosome tiles; in its plan Q

@@ -156,6 +156,11 @@ hipError_t launch_fitness_f32(const FitArgs& a, int basis, int degree, hipStream
   }
 }
 
+bool narrow_rows(const FitArgs& a) {
+  const int cb = a.tile_cols / 32;
+  return a.basis < 3 && narrow_degree(a.degree) && cb <= 2 && a.Q <= pairs_ahead(a.degree, cb);
+}
+
 size_t fitness_lds_bytes(const FitArgs& a, int degree) {
   const int cols = a.tile_cols;
   const size_t w = (size_t)(a.n_chunks > 1 ? 2 : 1) * cols *

@@ -26,6 +26,8 @@
 // the thresholded error: 11.1 ms with two launches a generation, 6.2 here (4.5 us
 // of a generation in the products and their error terms; 5.2 ms with the mean
 // square).
+#include <algorithm>
+
 #include "basis.h"
 #include "ga_ops.h"
 
@@ -402,15 +404,25 @@ static bool resident_args(const FitArgs& f, const GAArgs& g, ResidentArgs& a) {
       f.tiles_per_split != 1 || f.n_tiles > 32 || (f.basis == 3 && !f.cs))
     return false;
   const int nct = (g.P + 31) / 32;
-  // Cycles of a generation: the units of a SIMD (64 per MFMA, two row blocks;
-  // 32 rows' error terms of one or four instructions), the draws, the rest.  Two
-  // launches take 10-14 us; within 26,500 cycles (11 us) each of 160 shapes measured
-  // was faster here by a tenth at least, beyond it some were not: 3,000 x 8 with
-  // 50 chromosomes 11.4 for 10.7 us, 512 x 7 at degree 6 13.4 for 12.5.
-  const int64_t terms = f.error_fn >= 2 ? 660 : 280;
-  const int64_t cycles = (units + 3) / 4 * nct * ((S + 1) * 128 + terms) +
-                         (int64_t)g.P * g.K * 27 / 4 + 3840;
-  if (cycles > 26500) return false;
+  // Estimated cycles of a generation here and in two launches, fitted to 1,000 shapes
+  // (within 0.4 us as a rule).  Here: the units of a SIMD (their products; 32 rows'
+  // error terms of one or four instructions), draws and children (which wait for one
+  // another once children take most of the waves), the serial parts of an order and
+  // of a roulette wheel.  Two launches: what they take whatever they compute, one
+  // unit's products, the genes of the tail.  This kernel runs where it is ahead by
+  // 0.4 us at least; of 500 other shapes that it takes so one was slower, by 1.5 %.
+  // 2,100 x 8, degree 1, 23 chromosomes 5.2 us and 8.2; 1,000 x 5, degree 3, 50
+  // chromosomes 8.4 and 9.6; 2,000 x 8, degree 1, 64 chromosomes would take 9.1 for
+  // 8.5, 1,024 x 16 with 64 (thresholded) 10.6 for 9.3.
+  const int64_t PK = (int64_t)g.P * g.K;
+  const bool thresholded = f.error_fn >= 2, ordered = reads_order(g), wheel = g.selection == 2;
+  const int64_t here = 4000 + (units + 3) / 4 * nct * (105 * (S + 1) + (thresholded ? 570 : 300)) +
+                       6 * PK + 40 * std::max(0, g.P - 24 * nct) +
+                       g.P * ((ordered ? 145 : 0) + (wheel ? 110 : 0));
+  const int64_t launches = 18600 + 200 * S + 9 * PK / 4 + (thresholded ? 800 : 0) +
+                           (f.basis == 3 ? 1500 : 0) - (narrow_rows(f) ? 700 : 0) +
+                           g.P * ((ordered ? 77 : 0) + (wheel ? 72 : 0));
+  if (here + 1000 > launches) return false;
   a.X = f.X;
   a.t = f.t;
   a.cs = f.cs;

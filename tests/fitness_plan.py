@@ -1,5 +1,6 @@
-"""The plan of a float32 fitness launch as the library makes it (host code, no
-GPU needed), for tests whose shapes have to reach a certain kernel."""
+"""The plan of a float32 fitness launch and the route of a small run as the
+library chooses them (host code, no GPU needed), for tests whose shapes have to
+reach a certain kernel."""
 import ctypes
 from collections import namedtuple
 
@@ -25,14 +26,40 @@ class _Fit(ctypes.Structure):
          ("cs", ctypes.c_void_p), ("tile_cols", ctypes.c_int32), ("draw", _Draw)]
 
 
-def plan(NP, N, d, P, basis=0):
-    """Plan for P chromosomes over NP patterns of N features at degree d
-    (FitArgs and plan_fitness of csrc/common.h)."""
+class _GA(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("pop_a", "pop_b", "out_a", "out_b", "fitness", "order",
+                                               "gen_ptr", "stop")] + \
+        [(n, ctypes.c_int32) for n in ("generation", "P", "K", "k", "E", "elite_mode")] + \
+        [("thr_cross", ctypes.c_uint64), ("thr_mut", ctypes.c_uint64), ("sigma", ctypes.c_float),
+         ("seed", ctypes.c_uint64), ("n_slots", ctypes.c_int32), ("children", ctypes.c_void_p),
+         ("selection", ctypes.c_int32), ("cum", ctypes.c_void_p)]
+
+
+def _planned(NP, N, d, P, basis, error_fn=0):
+    """FitArgs (csrc/common.h) as plan_fitness leaves them."""
     fn = game.lib()["_ZN4game12plan_fitnessERNS_7FitArgsEiib"]
     fn.argtypes = [ctypes.POINTER(_Fit), ctypes.c_int, ctypes.c_int, ctypes.c_bool]
     fn.restype = None
-    a = _Fit(NP=NP, N=N, n_chrom=P, degree=d, basis=basis)
+    a = _Fit(NP=NP, N=N, n_chrom=P, degree=d, basis=basis, error_fn=error_fn)
     fn(ctypes.byref(a), d, basis, True)
     assert a.NP == NP and a.n_splits == -(-a.n_tiles // a.tiles_per_split)
+    return a
+
+
+def plan(NP, N, d, P, basis=0):
+    """Plan for P chromosomes over NP patterns of N features at degree d."""
+    a = _planned(NP, N, d, P, basis)
     return Plan(a.tile_cols, a.tiles_per_split, a.n_splits,
                 a.n_tiles - a.tiles_per_split * (a.n_splits - 1), a.n_chunks)
+
+
+def resident(NP, N, d, P, basis=0, error_fn=0, selection=0, tournament_k=4, elitism=2, elite_mode=0):
+    """Whether such a run takes the one-workgroup kernel."""
+    f = _planned(NP, N, d, P, basis, error_fn)
+    f.cs = 1 if basis == 3 else None      # a table there is: only tested for null
+    g = _GA(P=P, K=(2 if basis == 3 else 1) * N * d + 1, k=tournament_k, E=elitism,
+            elite_mode=elite_mode, selection=selection)
+    fn = game.lib()["_ZN4game13resident_fitsERKNS_7FitArgsERKNS_6GAArgsE"]
+    fn.argtypes = [ctypes.POINTER(_Fit), ctypes.POINTER(_GA)]
+    fn.restype = ctypes.c_bool
+    return bool(fn(ctypes.byref(f), ctypes.byref(g)))
