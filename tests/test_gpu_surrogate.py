@@ -332,3 +332,26 @@ def test_products_at_round_edges(gg, fp32, n_in, H, B):
     """Products whose waves take one round of 2 steps (K up to 256) or rounds
     of 4, with tiles, k blocks and minibatch ranges whole and ragged."""
     test_forward_and_gradients_match_oracle(gg, fp32, n_in, H, B)
+
+
+@pytest.mark.parametrize("fp32", [True, False])
+@pytest.mark.parametrize("n_in,H,B", [(40, 64, 4097), (29, 33, 5000)])
+def test_training_on_more_than_4096_rows(gg, fp32, n_in, H, B):
+    """Minibatches beyond the small-tile kernel: the forward layers and the
+    inner gradient on the LDS-tiled one, the weight gradients in ranges."""
+    test_forward_and_gradients_match_oracle(gg, fp32, n_in, H, B)
+
+
+def test_adam_step_on_more_than_4096_rows(gg):
+    rng = np.random.default_rng(6)
+    n_in, H, B = 29, 32, 4100
+    s = make(gg, n_in, True, H=H, minibatch=B, max_batch=B, lr=1e-2)
+    X = rng.uniform(-1, 1, (B, n_in)).astype(np.float32)
+    t = rng.normal(0, 1, B).astype(np.float32)
+    p = [np.asarray(x, np.float64) for x in split(s.params().cpu().numpy(), n_in, H)]
+    p, _, _ = mlp.adam_step(p, mlp.backward(p, X, t), [np.zeros_like(x) for x in p],
+                            [np.zeros_like(x) for x in p], 1, lr=1e-2)
+    s.train_step(torch.from_numpy(X).cuda(), torch.from_numpy(t).cuda())
+    for a, b in zip(split(s.params().cpu().numpy(), n_in, H), p):
+        assert rel_l2(a, b) < 1e-4
+    s.close()
