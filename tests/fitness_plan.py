@@ -63,3 +63,40 @@ def resident(NP, N, d, P, basis=0, error_fn=0, selection=0, tournament_k=4, elit
     fn.argtypes = [ctypes.POINTER(_Fit), ctypes.POINTER(_GA)]
     fn.restype = ctypes.c_bool
     return bool(fn(ctypes.byref(f), ctypes.byref(g)))
+
+
+# Shapes (NP, N, d, P) that reach a kernel or a branch of one, with the columns and
+# tiles per split, the last split's tiles and the gene chunks of their plans.
+REACHES = {
+    # 64-chromosome tiles: general rows, narrow rows by single features and by quads,
+    # one tile and more than one to a split
+    "64-general-1": ((100001, 20, 3, 40), (64, 1, 1, 1)),
+    "64-general-2": ((200001, 20, 1, 33), (64, 2, 2, 1)),
+    "64-general-quads-2": ((200001, 12, 4, 40), (64, 2, 2, 1)),
+    "64-narrow-quads-1": ((90001, 8, 1, 40), (64, 1, 1, 1)),
+    "64-narrow-quads-2": ((200001, 8, 1, 40), (64, 2, 2, 1)),
+    "64-narrow-rows-1": ((100001, 5, 3, 50), (64, 1, 1, 1)),
+    "64-narrow-rows-2": ((200001, 7, 4, 50), (64, 2, 2, 1)),
+    # 128-chromosome tiles: gene chunks over splits of 3 and of 4 tiles whose last one
+    # has 1 and 3 (a wave group without a tile joins the chunk barriers), whole genes
+    # over odd splits, an odd last feature pair at degree 4
+    "128-chunks-3-last-1": ((20000, 40, 9, 900), (128, 3, 1, 3)),
+    "128-chunks-4-last-3": ((100000, 40, 9, 256), (128, 4, 3, 3)),
+    "128-odd-5-last-2": ((40001, 9, 4, 1000), (128, 5, 2, 1)),
+    "128-pairs-of-quads-3": ((20001, 40, 2, 900), (128, 3, 1, 1)),
+    # 32-chromosome tiles, narrow rows over several tiles to a split: the next tile
+    # read ahead, quads and single features
+    "32-narrow-quads-2": ((300001, 16, 1, 23), (32, 2, 2, 1)),
+    "32-narrow-rows-2": ((300001, 15, 1, 23), (32, 2, 2, 1)),
+    "32-narrow-rows-5": ((600001, 7, 4, 20), (32, 5, 4, 1)),
+    "32-narrow-quads-d3": ((400001, 8, 3, 20), (32, 2, 1, 1)),
+}
+
+
+def reached(name, basis=0):
+    """The shape, after a check that its plan is still the one that it is for."""
+    shape, want = REACHES[name]
+    p = plan(*shape, basis)
+    chunks = 2 * want[3] if basis == 3 and want[3] > 1 else want[3]    # twice the terms
+    assert (p.cols, p.tiles_per_split, p.last_split, p.chunks) == (*want[:3], chunks), (name, p)
+    return shape

@@ -1,7 +1,7 @@
 """Launch plans of the float32 fitness (host code, no GPU needed)."""
 import pytest
 
-from fitness_plan import plan, resident
+from fitness_plan import REACHES, plan, reached, resident
 
 
 @pytest.mark.parametrize("NP,N,P,cols", [(6199, 28, 777, 128), (10933, 30, 404, 128),
@@ -24,3 +24,9 @@ def test_trigonometric_degree_1_avoids_narrow_tiles(NP, N, P, cols):
     ((1209, 4, 2, 64, dict(basis=2, error_fn=2, elite_mode=1)), False)])
 def test_one_workgroup_runs_where_it_is_faster(case, fits):
     assert resident(*case[:4], **case[4]) is fits
+
+
+@pytest.mark.parametrize("name", list(REACHES))
+def test_shapes_of_the_gpu_tests_reach_their_kernels(name):
+    for basis in (0, 1, 2):
+        reached(name, basis)

@@ -6,7 +6,7 @@ a relative bound with an absolute floor for fitness values near zero.
 import numpy as np
 import pytest
 
-from fitness_plan import plan
+from fitness_plan import plan, reached
 from oracle import game as og
 from paper_1304_0597_amd import datagen
 
@@ -63,8 +63,8 @@ SHAPES = [
     # few chromosomes over many patterns: hundreds of pattern splits
     (300001, 4, 2, 10),
     # 128-chromosome tiles over splits of 4 pattern tiles and a last split
-    # of 3 (the two wave groups of a workgroup walk unequal tile counts),
-    # with the genes in one chunk and in chunks (180 K-steps per lane half)
+    # of 3 (the two wave groups of a workgroup walk unequal tile counts), the
+    # genes in one chunk; narrow tiles of chunked genes (180 K-steps per lane half)
     (100000, 5, 3, 200), (100000, 40, 9, 150),
     # K-chunks through the two gene buffers over several tiles per split,
     # odd sub-feature count (zeroed half pair in the last chunk)
@@ -266,7 +266,7 @@ def test_trig_table_gives_the_kernels_own_bits(gg, shape):
 
 @pytest.mark.parametrize("basis", [0, 1, 2, 3])
 @pytest.mark.parametrize("shape", [
-    # NP, N, d, P: 32-, 64- and 128-chromosome tiles; feature quads whole and
+    # NP, N, d, P: 32- and 128-chromosome tiles; feature quads whole and
     # with a half-filled last group, rows that are no whole quads; genes in
     # chunks under narrow tiles, of whole quads and not; wide tiles of rows that
     # are pairs of quads
@@ -295,7 +295,7 @@ def test_tile_widths_and_feature_quads(gg, basis, shape):
 @pytest.mark.parametrize("basis", [0, 1, 2])
 @pytest.mark.parametrize("shape", [
     # NP, N, d, P: one feature, an odd last one, whole groups, one less than the
-    # group in quads and singly, single rows past a tile, one and two column blocks
+    # group in quads and singly, single rows past a tile, one to three 32-column tiles
     (1, 1, 1, 2), (257, 15, 1, 33), (9001, 16, 1, 23), (700, 12, 1, 64), (256, 8, 2, 32),
     (2000, 7, 4, 50), (511, 8, 4, 31), (300, 5, 3, 65), (640, 4, 3, 40)],
     ids=lambda s: "x".join(map(str, s)))
@@ -322,3 +322,63 @@ def test_split_sums_at_the_ends_of_their_rounds(gg, splits):
     X, t, W = problem(NP, 9, 2, 5, 0, seed=splits)
     _, f64 = gpu_fitness(gg, 0, 2, X, t, W)
     assert within(f64, og.fitness(X, t, W, 0, 2), t).all()
+
+
+def reference(X, t, W, basis, d, error_fn, R=0.49):
+    """Oracle errors and how far a float32 launch may be from them: the bound of
+    `within`, and for the thresholded errors the whole terms of patterns whose
+    residual lies within float32 rounding of the threshold."""
+    out = og.outputs(X, W, basis, d)
+    ref = og.error_from_outputs(out, t, min(error_fn, 2), R, literal_tmse=(error_fn == 3))
+    bound = 1e-5 * np.abs(ref) + 1e-7 * float(np.mean(t.astype(np.float64) ** 2))
+    if error_fn >= 2:
+        r = t.astype(np.float64)[:, None] - out
+        q = np.abs(r) if error_fn == 2 else r * r
+        near = np.abs(q - R) <= 1e-5 * np.maximum(1.0, np.abs(q))
+        bound = bound + (near * (r * r)).sum(axis=0) / X.shape[0]
+    return ref, bound
+
+
+@pytest.mark.parametrize("basis", [0, 1, 2, 3])
+@pytest.mark.parametrize("name", ["64-general-1", "64-general-2", "64-general-quads-2",
+                                  "64-narrow-quads-1", "64-narrow-quads-2", "64-narrow-rows-1",
+                                  "64-narrow-rows-2"])
+def test_64_chromosome_tiles(gg, basis, name):
+    """Against the oracle, and from an X off its 16-byte boundary."""
+    test_tile_widths_and_feature_quads(gg, basis, reached(name, basis))
+
+
+@pytest.mark.parametrize("basis", [0, 1, 2, 3])
+@pytest.mark.parametrize("name", ["128-chunks-3-last-1", "128-chunks-4-last-3", "128-odd-5-last-2",
+                                  "128-pairs-of-quads-3"])
+def test_128_chromosome_tiles_of_unequal_streams(gg, basis, name):
+    test_tile_widths_and_feature_quads(gg, basis, reached(name, basis))
+
+
+@pytest.mark.parametrize("basis", [0, 1, 2])
+@pytest.mark.parametrize("name", ["32-narrow-quads-2", "32-narrow-rows-2", "32-narrow-rows-5",
+                                  "32-narrow-quads-d3", "64-narrow-quads-2", "64-narrow-rows-2"])
+def test_narrow_rows_over_several_tiles(gg, basis, name):
+    """Every error function has a tile loop of its own."""
+    NP, N, d, P = reached(name, basis)
+    X, t, W = problem(NP, N, d, P, basis, seed=NP + d, binary=True)
+    W *= 0.3
+    for error_fn in range(4):
+        f32, f64 = gpu_fitness(gg, basis, d, X, t, W, error_fn)
+        ref, bound = reference(X, t, W, basis, d, error_fn)
+        assert np.all(np.abs(f64 - ref) <= bound), (error_fn, np.max(np.abs(f64 - ref) / ref))
+        assert np.array_equal(f32, f64.astype(np.float32))
+
+
+@pytest.mark.parametrize("name", ["64-narrow-rows-1", "64-general-1", "128-odd-5-last-2"])
+def test_non_finite_genes_in_wider_tiles(gg, name):
+    """A chromosome with a NaN or infinite gene ends at +inf over a ragged last
+    tile, and its neighbours keep their oracle values."""
+    NP, N, d, P = reached(name)
+    X, t, W = problem(NP, N, d, P, 0, seed=12)
+    bad = [1, P // 2, P - 1]
+    W[bad[0], 4], W[bad[1], 7], W[bad[2], 0] = np.nan, -np.inf, np.inf
+    f32, f64 = gpu_fitness(gg, 0, d, X, t, W)
+    assert np.all(np.isposinf(f32[bad])) and np.all(np.isposinf(f64[bad]))
+    good = np.setdiff1d(np.arange(P), bad)
+    assert within(f64[good], og.fitness(X, t, W[good], 0, d), t).all()
