@@ -4,6 +4,7 @@ device's own fitness vectors."""
 import numpy as np
 import pytest
 
+from fitness_plan import plan
 from oracle import ga as oga
 from oracle import game as og
 from paper_1304_0597_amd import datagen
@@ -297,7 +298,8 @@ def test_selection_modes_in_the_loop(gg, selection):
 
 
 # (NP, N, d, P) and the pattern splits the plan gives them: at most 64 and
-# more than 64, with 64- and 128-chromosome tiles, ragged last workgroups.
+# more than 64, with 32-, 64- and (40,000 patterns) 128-chromosome tiles, ragged
+# last workgroups.
 SPLIT_SHAPES = [((2000, 7, 4, 50), "8-splits"), ((5000, 8, 4, 300), "20-splits-128-wide"),
                 ((100000, 5, 3, 50), "391-splits"), ((40000, 8, 4, 300), "79-splits-128-wide")]
 
@@ -427,4 +429,15 @@ def test_whole_runs_equal_their_generations(gg, case):
     (700, 20, 4, 193, dict(elite_mode=1, elitism=0))],
     ids=lambda c: f"{c[0]}x{c[1]}-d{c[2]}-P{c[3]}-" + "-".join(f"{k}{v}" for k, v in c[4].items()))
 def test_generation_tail_with_its_rank_order(gg, case):
+    test_generation_tail_at_its_edges(gg, case)
+
+
+@pytest.mark.parametrize("case", [
+    # partials summed inside the one-launch tail by 64 lanes a chromosome: 33, 47 and
+    # 64 splits, the last with four rounds of the workgroup full
+    (8193, 8, 1, 50, {}), (12000, 8, 1, 50, dict(error_fn=2)),
+    (16384, 7, 2, 64, dict(selection=2)), (8200, 3, 2, 63, dict(selection=1, error_fn=1))],
+    ids=lambda c: f"{c[0]}x{c[1]}-d{c[2]}-P{c[3]}-" + "-".join(f"{k}{v}" for k, v in c[4].items()))
+def test_generation_tail_with_64_lanes_a_sum(gg, case):
+    assert 33 <= plan(*case[:4]).splits <= 64
     test_generation_tail_at_its_edges(gg, case)
