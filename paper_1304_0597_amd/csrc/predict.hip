@@ -104,6 +104,48 @@ __global__ __launch_bounds__(kRows) void predict_kernel(PredictArgs a) {
   }
 }
 
+// Outputs of one chromosome (blockIdx.y) on narrow rows (own_rows): a thread reads
+// its own row and walks over the patterns, the genes in LDS once.  A tile is so
+// little work there that staging its rows, and a workgroup for each tile, cost
+// more than the outputs.  1,000,000 patterns: 1 feature, power degree 1, one
+// chromosome 4.5 us, 8.7 in staged tiles; 4 features, power 4, two 10.6 and 11.8; 8
+// features, power 1, two 7.6 and 12.8.
+template <int BASIS, int D>
+__global__ __launch_bounds__(kRows) void predict_rows_kernel(PredictArgs a) {
+  constexpr int B = BASIS == 3 ? 2 : 1;
+  extern __shared__ float w[];
+  const int N = a.N;
+  for (int i = threadIdx.x; i < a.K; i += kRows) w[i] = a.genes[(int64_t)blockIdx.y * a.K + i];
+  __syncthreads();
+  float* out_c = a.out + (int64_t)blockIdx.y * a.NP;
+  for (int64_t k = (int64_t)blockIdx.x * kRows + threadIdx.x; k < a.NP;
+       k += (int64_t)gridDim.x * kRows) {
+    const float* row = a.X + k * N;
+    float out = w[0];
+    for (int f = 0; f < N; ++f) {
+      const float x = row[f];
+      const float* g = w + 1 + f * B * D;
+      float c = 0.f, s = 0.f;
+      if constexpr (BASIS == 3) sincosf(x, &s, &c);
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        Recur<BASIS> rc;
+        if constexpr (BASIS == 3) rc.seed_cs(c, s, b);
+        else rc.seed(x, 0);
+        auto term = [&](auto jc) {
+          constexpr int j = decltype(jc)::value;
+          out = fmaf(g[b * D + j], rc.cur, out);
+          if constexpr (j + 1 < D) rc.template advance<j + 1>(x);
+        };
+        [&]<int... J>(std::integer_sequence<int, J...>) {
+          (term(std::integral_constant<int, J>{}), ...);
+        }(std::make_integer_sequence<int, D>{});
+      }
+    }
+    out_c[k] = out;
+  }
+}
+
 // Counts per chromosome, integer sums: exact in any order.  A workgroup
 // takes several tiles of its chromosome group and adds its counts once.  With
 // a.tally set each addition also counts its workgroup in the word's top 16
@@ -202,6 +244,24 @@ hipError_t launch_variant(PredictArgs a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Rows that each thread reads for itself, one chromosome at a time: those narrow
+// enough for their cache lines to be used while they are there, as far as reading
+// them again for each chromosome stays below what staging costs.  1,000,000
+// patterns, power 1: 8 features, one chromosome 6.2 us (9.1 staged), two 7.6 (12.8),
+// four 11.5 (13.5, but other degrees up to 26 % slower so); 12, one 13.2 (12.7); 3,
+// four 11.0 (11.8).  With a sine and cosine for every read, 8 features of one
+// chromosome take up to 30 % longer, 3 features of four 6 to 24.  Up to one and a
+// half tiles a CU staging covers less: 66,000 patterns, 12 features, one chromosome 3.5
+// us (4.5), 5 of four 3.9 (4.4).  Classification has more to do per tile: 1,000,000
+// patterns, 1 feature, one chromosome 16.9 us (20.4), two 26.3 (19.7).
+bool own_rows(const PredictArgs& a, int64_t tiles, bool trig) {
+  const bool few = tiles < 384;
+  if (a.counts) return a.n == 1 && a.N <= (trig ? 4 : 16);
+  if (trig) return a.n <= 2 ? a.N <= 4 : a.N <= 3 && a.n * a.N <= 8;
+  if (a.n <= 2) return a.N <= (few ? 16 : 8);
+  return few ? a.N <= 6 && a.n * a.N <= 36 : a.N <= 3 && a.n * a.N <= 12;
+}
+
 // Chromosomes per thread: one when groups of 8 would leave most CUs without
 // a workgroup (2,100 x 11 patterns, 23 chromosomes: 6.1 us against 11.5),
 // otherwise groups of 4 or 8 (1,000,000 x 20, 5 chromosomes: 59 us for two
@@ -209,7 +269,15 @@ hipError_t launch_variant(PredictArgs a, hipStream_t s) {
 template <int BASIS, int D>
 hipError_t launch_degree(const PredictArgs& a, hipStream_t s) {
   const int64_t tiles = (a.NP + kRows - 1) / kRows;
-  if (!stages_rows(tiles * ((a.n + 7) / 8))) return launch_variant<BASIS, D, 1, false>(a, s);
+  const bool own = own_rows(a, tiles, BASIS == 3);
+  if (!stages_rows(tiles * ((a.n + 7) / 8)) || (own && a.counts))
+    return launch_variant<BASIS, D, 1, false>(a, s);
+  if (own) {
+    hipLaunchKernelGGL((predict_rows_kernel<BASIS, D>),
+                       dim3((unsigned)std::min<int64_t>(tiles, 1024), (unsigned)a.n), dim3(kRows),
+                       (size_t)a.K * sizeof(float), s, a);
+    return hipGetLastError();
+  }
   if (a.n == 1) return launch_variant<BASIS, D, 1, true>(a, s);
   return a.n <= 4 ? launch_variant<BASIS, D, 4, true>(a, s)
                   : launch_variant<BASIS, D, 8, true>(a, s);

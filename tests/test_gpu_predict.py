@@ -166,3 +166,25 @@ def test_predict_beyond_2_to_the_32_patterns(gg):
         n = min(step, NP - r)
         assert torch.equal(out[0, r:r + n], X[r:r + n, 0] * 2 + 0.5), r
     g.close()
+
+
+@pytest.mark.parametrize("basis,d", [(0, 4), (1, 3), (2, 1), (2, 16), (3, 1), (3, 8)])
+@pytest.mark.parametrize("N", [1, 3, 4, 5, 8, 9, 16, 17])
+def test_narrow_rows_predict_the_same_bits_alone_and_together(gg, basis, d, N):
+    """Chromosomes by ones, twos, threes, fours and thirteens over more tiles than
+    CUs, narrow rows and wider ones: one way of reading them or another, the same
+    outputs, and class counts that are their decisions."""
+    NP = 70001
+    X, t, g = make(gg, basis, d, NP, N, P=13, seed=N + d)
+    genes = np.random.default_rng(N).uniform(-0.5, 0.5, (13, g.n_genes)).astype(np.float32)
+    gd = torch.from_numpy(genes).cuda()
+    together = g.predict(gd)
+    ref = og.outputs(X, genes, basis, d).T
+    assert np.all(np.abs(together.cpu().numpy() - ref) <= bound(genes, g.n_genes, d)[:, None])
+    for n in (1, 2, 3, 4):
+        for first in (0, 13 - n):
+            assert torch.equal(g.predict(gd[first:first + n].contiguous()),
+                               together[first:first + n]), n
+    alone = g.classify(gd[5:6].contiguous(), threshold=0.1).cpu().numpy()
+    assert np.array_equal(alone, _counts_from(together[5:6].cpu().numpy(), t, 0.1))
+    g.close()
