@@ -81,7 +81,7 @@ __device__ __forceinline__ void sincos_of(float xf, double& sn, double& cs) {
   cs = ((q + 1) & 2) ? -c0 : c0;
 }
 
-template <int D, bool STAGE>
+template <int D, bool STAGE, bool LDS_OUT>
 __global__ __launch_bounds__(kRows) void trig_sums_kernel(const float* X, int64_t NP, int N,
                                                           float* Z) {
   extern __shared__ float rows[];
@@ -124,13 +124,15 @@ __global__ __launch_bounds__(kRows) void trig_sums_kernel(const float* X, int64_
       }
     }
   }
-  __syncthreads();
-  float* z = rows + threadIdx.x * SZ;
+  if constexpr (LDS_OUT) __syncthreads();
+  else if ((int)threadIdx.x >= n_rows) return;
+  float* z = LDS_OUT ? rows + threadIdx.x * SZ : Z + (row0 + threadIdx.x) * (2 * D);
 #pragma unroll
   for (int j = 0; j < D; ++j) {
     z[j] = (float)c[j];
     z[D + j] = (float)s[j];
   }
+  if constexpr (!LDS_OUT) return;
   __syncthreads();
   for (int e = threadIdx.x; e < n_rows * 2 * D; e += kRows)
     Z[row0 * (2 * D) + e] = rows[e / (2 * D) * SZ + e % (2 * D)];
@@ -139,19 +141,30 @@ __global__ __launch_bounds__(kRows) void trig_sums_kernel(const float* X, int64_
 // Rows of up to one cache line, and those of few workgroups, are read by their
 // threads directly (1,792,000 x 11: staging them costs 10 us of 60; 200,000 x 64
 // takes 47 us staged and 73 was the cost of strided reads).
-template <int D>
-hipError_t launch_d(const float* X, int64_t NP, int N, float* Z, hipStream_t s) {
+template <int D, bool LDS_OUT>
+hipError_t launch_out(const float* X, int64_t NP, int N, float* Z, hipStream_t s) {
   const dim3 grid((unsigned)((NP + kRows - 1) / kRows));
-  const int stride = row_stride(2 * D);
+  const int out = LDS_OUT ? row_stride(2 * D) : 0;
   if (N <= 16 || !stages_rows(grid.x)) {
-    hipLaunchKernelGGL((trig_sums_kernel<D, false>), grid, dim3(kRows),
-                       (size_t)kRows * stride * sizeof(float), s, X, NP, N, Z);
+    hipLaunchKernelGGL((trig_sums_kernel<D, false, LDS_OUT>), grid, dim3(kRows),
+                       (size_t)kRows * out * sizeof(float), s, X, NP, N, Z);
   } else {
-    const int most = std::max(stride, row_stride(std::min(N, kChunk)));
-    hipLaunchKernelGGL((trig_sums_kernel<D, true>), grid, dim3(kRows),
+    const int most = std::max(out, row_stride(std::min(N, kChunk)));
+    hipLaunchKernelGGL((trig_sums_kernel<D, true, LDS_OUT>), grid, dim3(kRows),
                        (size_t)kRows * most * sizeof(float), s, X, NP, N, Z);
   }
   return hipGetLastError();
+}
+
+// Sums of up to 32 bytes a pattern are whole sectors as their threads store them, and
+// with fewer workgroups than CUs nothing covers a turn through LDS: 8,000 x 1, degree
+// 12 3.0 us, 3.7 through it, but 84,086 x 1 5.6 and 4.8, 60,000 x 1, degree 8 3.7 and
+// 3.4; degree 3, 84,086 x 2 3.2 and 3.5, 800,000 x 2 7.8 and 8.9.
+template <int D>
+hipError_t launch_d(const float* X, int64_t NP, int N, float* Z, hipStream_t s) {
+  if constexpr (D > 4)
+    if (NP > 192 * kRows) return launch_out<D, true>(X, NP, N, Z, s);
+  return launch_out<D, false>(X, NP, N, Z, s);
 }
 
 template <int... Ds>

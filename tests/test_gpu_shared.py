@@ -146,3 +146,10 @@ def test_trig_sums_over_all_angles(gg, d, NP, N):
         X[0, 0], X[1, N - 1] = np.inf, np.nan
         Z2 = gg.game_trig_sums(torch.from_numpy(X).cuda(), d).cpu().numpy().astype(np.float64)
         assert np.isnan(Z2[:2]).all() and np.array_equal(Z2[2:], Z[2:])
+
+
+@pytest.mark.parametrize("d", [1, 4, 5, 16])
+@pytest.mark.parametrize("NP,N", [(300, 1), (49152, 2), (49153, 2), (70001, 16), (65280, 17)])
+def test_trig_sums_stored_directly_and_through_lds(gg, d, NP, N):
+    """Both sides of the degree and of the size from which sums go out through LDS."""
+    test_trig_sums_over_all_angles(gg, d, NP, N)
