@@ -138,14 +138,17 @@ __global__ __launch_bounds__(kRows) void trig_sums_kernel(const float* X, int64_
     Z[row0 * (2 * D) + e] = rows[e / (2 * D) * SZ + e % (2 * D)];
 }
 
-// Rows of up to one cache line, and those of few workgroups, are read by their
-// threads directly (1,792,000 x 11: staging them costs 10 us of 60; 200,000 x 64
-// takes 47 us staged and 73 was the cost of strided reads).
+// Rows of up to one cache line, those of few workgroups and inputs of up to 14 MB,
+// whose lines stay cached between a thread's reads of them, are read by their
+// threads directly.  Degree 3 direct and staged: 84,086 x 17 6.5 us and 9.1, 84,086
+// x 40 15.5 and 16.8, 150,000 x 32 21.6 and 17.6; 1,792,000 x 11: staging costs 10
+// us of 60; 200,000 x 64 takes 47 staged, 73 with strided reads.
+constexpr int64_t kDirectReads = 3500000;  // floats
 template <int D, bool LDS_OUT>
 hipError_t launch_out(const float* X, int64_t NP, int N, float* Z, hipStream_t s) {
   const dim3 grid((unsigned)((NP + kRows - 1) / kRows));
   const int out = LDS_OUT ? row_stride(2 * D) : 0;
-  if (N <= 16 || !stages_rows(grid.x)) {
+  if (N <= 16 || NP * N <= kDirectReads || !stages_rows(grid.x)) {
     hipLaunchKernelGGL((trig_sums_kernel<D, false, LDS_OUT>), grid, dim3(kRows),
                        (size_t)kRows * out * sizeof(float), s, X, NP, N, Z);
   } else {

@@ -153,3 +153,10 @@ def test_trig_sums_over_all_angles(gg, d, NP, N):
 def test_trig_sums_stored_directly_and_through_lds(gg, d, NP, N):
     """Both sides of the degree and of the size from which sums go out through LDS."""
     test_trig_sums_over_all_angles(gg, d, NP, N)
+
+
+@pytest.mark.parametrize("d", [2, 6])
+@pytest.mark.parametrize("NP,N", [(65537, 53), (66037, 53), (66038, 53), (70000, 51)])
+def test_trig_sums_read_directly_and_through_lds(gg, d, NP, N):
+    """Both sides of the input size from which long rows are read through LDS."""
+    test_trig_sums_over_all_angles(gg, d, NP, N)
