@@ -214,10 +214,10 @@ int game_step(game_t h);
  * the device stop flag, written to the host after each chunk, shows the run
  * stopped (chunks queued meanwhile do nothing).  The smallest float32 runs
  * (at most 64 chromosomes, the expanded data set within one CU's LDS) go
- * through up to 1,024 generations per launch of one workgroup instead.  With a surrogate attached the
- * generations are queued on the stream directly, 8 per chunk, with the same
- * stop checks (its few hundred short launches per generation run faster
- * that way).  Synchronises the stream.  max_generations < 0 and target < 0
+ * through up to 1,024 generations per launch of one workgroup instead, where that is
+ * the faster way.  With a surrogate attached the generations are queued on the
+ * stream directly, 8 per chunk, with the same stop checks (its few hundred short
+ * launches per generation run faster that way).  Synchronises the stream.  max_generations < 0 and target < 0
  * keep the configured values; a run that stopped on earlier limits resumes
  * when its last evaluation no longer meets the new ones, and continues from
  * that evaluation exactly as one uninterrupted run would have; otherwise

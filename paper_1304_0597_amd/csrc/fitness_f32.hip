@@ -203,9 +203,9 @@ void plan_fitness(FitArgs& a, int degree, int basis, bool wide) {
   // workgroups of 128 chromosomes and 13 in 64 of 32; 200,000 x 20 with 2,048
   // take 980 in 128s, 1,046 in 64s and 1,091 in 32s.  All workgroups of a
   // launch are resident at once (one of eight waves per CU, two or four of four
-  // waves): splits are rounded down to that, since a few workgroups more run a
-  // round of their own (100,000 x 32, Chebyshev 10, 1,500 chromosomes: 1,615 us
-  // in 264 workgroups, 850 in 252).
+  // waves; launches of few terms run two rounds of four): splits are rounded down
+  // to that, since a few workgroups more run a round of their own (100,000 x 32,
+  // Chebyshev 10, 1,500 chromosomes: 1,615 us in 264 workgroups, 850 in 252).
   int best_cb = 2, best_tps = 1;
   int64_t best = INT64_MAX;
   for (int cb = 4; cb >= 1; cb >>= 1) {

@@ -229,8 +229,8 @@ __device__ __forceinline__ void fitness_f32_block(const FitArgs& a_in, const flo
     }
     if constexpr (kQuads) {
       if (quads) {
-        // Half h reads the quad 2 q0 + 8 k + 4 h .. + 3 of its row; unpack_x
-        // exchanges the halves' words.
+        // Half h reads the quad 2 q0 + 8 k + 4 h .. + 3 of its row; the halves'
+        // words are exchanged (swap_halves) where a tile's values are next used.
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
           const int64_t r = row_of(tile, rb);

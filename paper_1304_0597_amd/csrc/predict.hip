@@ -12,7 +12,8 @@
 // by scalar loads, one SGPR operand per multiply-add; the degree is a
 // template argument, so the recurrence's coefficients are constants.  The
 // patterns' rows are read in consecutive addresses into LDS (odd row stride:
-// conflict-free) and serve every chromosome group of the workgroup.  Bound
+// conflict-free) and serve every chromosome group of the workgroup; narrow rows
+// and those of few workgroups each thread reads for itself.  Bound
 // by the vector multiply-adds for 8 chromosomes and by reading the patterns
 // for one.  1,000,000 x 20 patterns, Legendre 8: 25 us for one chromosome
 // (80 MB of patterns, 4 MB of outputs: 3.4 TB/s), 57 us for 8, 367 us for 64
@@ -247,13 +248,13 @@ hipError_t launch_variant(PredictArgs a, hipStream_t s) {
 // Rows that each thread reads for itself, one chromosome at a time: those narrow
 // enough for their cache lines to be used while they are there, as far as reading
 // them again for each chromosome stays below what staging costs.  1,000,000
-// patterns, power 1: 8 features, one chromosome 6.2 us (9.1 staged), two 7.6 (12.8),
-// four 11.5 (13.5, but other degrees up to 26 % slower so); 12, one 13.2 (12.7); 3,
-// four 11.0 (11.8).  With a sine and cosine for every read, 8 features of one
+// patterns, power 1: 8 features, one chromosome 5.5 us (9.1 staged), two 7.6 (12.6),
+// four 11.5 (13.5, but other degrees up to 26 % slower so); 12, one 13.2 (12.6); 3,
+// four 10.2 (11.9).  With a sine and cosine for every read, 8 features of one
 // chromosome take up to 30 % longer, 3 features of four 6 to 24.  Up to one and a
-// half tiles a CU staging covers less: 66,000 patterns, 12 features, one chromosome 3.5
-// us (4.5), 5 of four 3.9 (4.4).  Classification has more to do per tile: 1,000,000
-// patterns, 1 feature, one chromosome 16.9 us (20.4), two 26.3 (19.7).
+// half tiles a CU staging covers less: 66,000 patterns, 12 features, one chromosome 3.4
+// us (4.5), 5 of four 3.7 (4.3).  Classification has more to do per tile: 1,000,000
+// patterns, 1 feature, one chromosome 17.0 us (20.5), two 26.3 (19.7).
 bool own_rows(const PredictArgs& a, int64_t tiles, bool trig) {
   const bool few = tiles < 384;
   if (a.counts) return a.n == 1 && a.N <= (trig ? 4 : 16);

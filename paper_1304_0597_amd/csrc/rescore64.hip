@@ -11,10 +11,10 @@
 //
 // Bound by the float64 multiply-adds and the gene conversions, one of each
 // per term next to the recurrence's, with the patterns' read under them.
-// 250,000 x 32 patterns, Chebyshev 8, one chromosome: 15.6 us and 3.3 for
-// the finish pass (37.5 in all with 256 blocks reading rows thread by thread
-// and one thread adding their partials); 1,000,000 x 32: 54 us against 80
-// (2.4 TB/s of patterns, 64 chromosomes 1.33 ms against 4.8).  Publishing
+// 250,000 x 32 patterns, Chebyshev 8, one chromosome: 15.7 us with the finish
+// pass (37.5 with 256 blocks reading rows thread by thread and one thread
+// adding their partials); 1,000,000 x 32: 54 us against 80 (2.4 TB/s of
+// patterns, 64 chromosomes 1.33 ms against 4.8).  Publishing
 // the partials to a last block with device-scope atomics instead of a second
 // launch was slower (24.4 us): its round trips are serial.
 #include <algorithm>

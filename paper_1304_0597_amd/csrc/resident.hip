@@ -1,7 +1,7 @@
 // Whole runs of the smallest problems in one workgroup.
 //
 // A generation of a small run is a fitness launch and a tail launch
-// (ga.hip), about 5 us each whatever they compute.  When the expanded data
+// (ga.hip), 4 to 5 us each whatever they compute.  When the expanded data
 // set fits one CU's LDS and the products are a few microseconds of that CU,
 // one workgroup runs generation after generation with barriers in place of
 // launches:
@@ -22,10 +22,9 @@
 // Products, sums and operators are taken in the order of the fitness kernel
 // and the two-launch generation, so a run has the same bits on either path.
 //
-// 2,100 patterns x 8 features, degree 1, 23 chromosomes, 1,000 generations with
-// the thresholded error: 11.1 ms with two launches a generation, 6.2 here (4.5 us
-// of a generation in the products and their error terms; 5.2 ms with the mean
-// square).
+// 2,100 patterns x 8 features, degree 1, 23 chromosomes, 1,000 generations: 8.2 ms
+// with two launches a generation and 5.2 here with the mean square, 6.2 with the
+// thresholded error (4.5 us of a generation in the products and their error terms).
 #include <algorithm>
 
 #include "basis.h"
